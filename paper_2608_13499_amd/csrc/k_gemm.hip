@@ -34,6 +34,7 @@ namespace {
 
 constexpr int kNumCUs = 256;  // MI355X compute units
 constexpr int64_t kGroupBytes = (int64_t)16 << 20;  // x rows per tile group (see tile_group_rows)
+constexpr int64_t kW4MaxN = (int64_t)1 << 22;  // the four-wave kernel's 32-bit offsets into 256 rows of y
 constexpr int64_t kSplitKMaxM = 2048;  // split-K is for small M (decode batches)
 
 // Tile configuration: BM x BN block tile, K in slices of BK, WGM x WGN waves
@@ -535,78 +536,148 @@ __device__ __forceinline__ f32x4 agpr_read(const f32x4& acc) {
   return v;
 }
 
+// acc <- 0 by a small MFMA on zero operands: the matrix core is idle in the
+// epilogue, and the accumulator stays the AGPR tuple it is (zeroed in C++ it
+// got VGPR homes and spilled).
+__device__ __forceinline__ void agpr_zero(f32x4& acc, const u32x2& zero) {
+  asm volatile("v_mfma_f32_4x4x4_16b_f16 %0, %1, %1, 0" : "+a"(acc) : "v"(zero));
+}
+
+// Order a scalar or vector value among the other assembly statements: work on
+// it between two pins stays between the MFMAs it is written between.
+template <class V>
+__device__ __forceinline__ void pin_s(V& v) {
+  asm volatile("" : "+s"(v));
+}
+template <class V>
+__device__ __forceinline__ void pin_v(V& v) {
+  asm volatile("" : "+v"(v));
+}
+
 // The 256x256 tile as four waves of 128x128, one wave per SIMD.  With two
 // waves per SIMD (gemm_bf16_kernel's eight-wave form) the older wave takes
 // the matrix core first and then waits at the slice barrier while the younger
 // one finishes alone; here every SIMD runs one wave and the slice's fragment
-// reads fall from 192 to 128 KB per workgroup.  Swizzle, loads, split tail
-// and epilogue are those of gemm_bf16_kernel.  A k-step is 64 MFMAs; the 16
-// fragment reads of the next k-step go one after each of its first 16 MFMAs
-// (in the order the next k-step consumes them), and in the last k-step of a
-// slice 16 loads go one after every fourth MFMA.
+// reads fall from 192 to 128 KB per workgroup.
+//
+// What bounds it: one wave issues everything, about one instruction every 4
+// cycles, and a 16x16x32 MFMA takes 16, so more than three other instructions
+// between two MFMAs leave the matrix core idle.  Hence:
+//  * a tile load is two instructions (M0, the load): its per-lane offset is
+//    constant, the descriptor's base moves along K once per slice in scalar
+//    registers.  (Offsets computed per load in vector registers cost the 8871
+//    x 28672 x 4096 gate-up 1587 against 1480 us, the same card.)
+//  * a k-step is 64 MFMAs; the 16 fragment reads of the next k-step go one
+//    after every second MFMA of the first half, 8 tile loads one after every
+//    eighth MFMA (spread over both k-steps of a slice: 1480 -> 1454 us, the
+//    14336-long down projection 757 -> 705);
+//  * everything else (descriptor, ring and address updates) is pinned between
+//    MFMAs, a few instructions at a place; a slice ends in a wait and a branch
+//    (1451 -> 1430 us, 16384 x 57344 x 8192 10300 -> 9850).
 //
 // The LDS ring is five 32 KB half-slices (160 KB) rather than two 64 KB
 // slices: the x half and the W half of a slice rotate through the buffers
-// separately, so once slice kt is read its buffers take the W half of slice
-// kt + 2 and the x half of slice kt + 3.  About 1.5 slices (96 KB) are in
-// flight per CU instead of at most one, and the x halves get two slices of
-// time to land.  The loads are latency bound: the tile-load pattern alone
-// moves 18 TB/s over the chip this way against 13.7 TB/s with two stages.
-template <class C, bool XLEAD>
+// separately.  The lead operand's half of slice s + 2 is loaded during the
+// first k-step of slice s (into the buffer slice s - 1 freed), the other
+// operand's during the second, so 1 to 1.5 slices are in flight per CU.
+//
+// A workgroup runs a chain of up to kChain tiles: the loads run on into the
+// next tile's first slices while the last ones of this tile are used, and the
+// stores of a tile drain under the next one's first slice.  A tile of its own
+// pays the first loads' latency and the drain each time (about 10 of the 93
+// us of a K = 4096 tile; gate-up 1532 -> 1497 us, QKV 343 -> 338, O 234 -> 232,
+// long K unchanged).  The chain is short so that a launch on a CU-masked
+// stream, or beside other work, still balances over whatever CUs it gets.
+//
+// The columns of a W fragment pair are interleaved in runs of four (fragment
+// i, row f: column 32 (i / 2) + 8 (f / 4) + 4 (i & 1) + f % 4), so a lane's
+// two accumulators hold eight consecutive columns: one 16-byte store.  The W
+// rows are swizzled by that row's place in the fragment, as the x rows are.
+constexpr int kChain = 4;
+template <class C, bool XLEAD, bool RAGGED_K>
 __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf16* __restrict__ x,
                                                                       const __bf16* __restrict__ W,
                                                                       const __bf16* __restrict__ bias,
                                                                       __bf16* __restrict__ y, int M, int N,
                                                                       int K_total, int group_m, int kchunk,
-                                                                      float* __restrict__ part, GroupedGemm,
-                                                                      int dp_cnt, int tail_cnt) {
+                                                                      float* __restrict__ part, int dp_cnt,
+                                                                      int tail_cnt, int items, int chain) {
   static_assert(C::kWaves == 4 && C::WM == 128 && C::WN == 128 && !C::DEEP, "four waves of 128x128");
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  OPS_LDS char* smem = (OPS_LDS char*)smem_raw;
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, WM = C::WM, WN = C::WN;
   constexpr int MI = 16, TM = WM / MI, TN = WN / MI, KS = BK / 32;
+  constexpr int LX = BM / C::kRowsPerLoad / C::kWaves, LW = BN / C::kRowsPerLoad / C::kWaves;
+  static_assert(KS == 2, "two k-steps per slice");
+  static_assert(BM == BN && LX == 8 && LW == 8, "square tile: x and W halves of 8 loads per wave");
+  constexpr int kStores = TM * TN / 2;  // 16-byte stores of a tile per lane
+  constexpr uint32_t kOutOfRange = 0xfffffff0u;
 
   const int tiles_n = (N + BN - 1) / BN;
   const int tiles_m = (M + BM - 1) / BM;
   const int tiles = tiles_m * tiles_n;
   const int ld = K_total;
-  int split = 0, kc = kchunk;
-  float* tile_part = nullptr;
-  uint32_t tid;
-  if (tail_cnt == 0) {
-    split = blockIdx.x / tiles;
-    tid = xcd_remap(blockIdx.x - split * tiles, (uint32_t)tiles);
-  } else if ((int)blockIdx.x < dp_cnt) {
-    tid = xcd_remap(blockIdx.x, (uint32_t)dp_cnt);
-    kc = K_total;
-  } else {
-    const int b = blockIdx.x - dp_cnt;
-    split = b / tail_cnt;
-    const int t = (int)xcd_remap(b - split * tail_cnt, (uint32_t)tail_cnt);
-    tid = dp_cnt + t;
-    tile_part = part + ((int64_t)split * tail_cnt + t) * BM * BN;
-  }
-  int tm, tn;
-  tile_coords(tid, tiles_m, tiles_n, group_m, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int m_rows = min(BM, M - m0);
-  const int k_begin = split * kc;
-  const int K = min(K_total - k_begin, kc);
+
+  // One work item: a tile and its K range.
+  struct Item {
+    uint64_t xb, wb;      // the tile's first x and W row at the range's first k
+    uint32_t xrec, wrec;  // bytes addressable from there: rows past the tile's end read zeros
+    int K;                // length of the range
+    int m0, n0, m_rows, split;
+    float* tile_part;     // split tail: the compact fp32 partial tile
+  };
+  auto decode = [&](int id) {
+    Item it;
+    it.split = 0;
+    it.tile_part = nullptr;
+    int kc = kchunk;
+    uint32_t tid;
+    if (tail_cnt == 0) {
+      it.split = id / tiles;
+      tid = xcd_remap(id - it.split * tiles, (uint32_t)tiles);
+    } else if (id < dp_cnt) {
+      tid = xcd_remap(id, (uint32_t)dp_cnt);
+      kc = K_total;
+    } else {
+      const int b = id - dp_cnt;
+      it.split = b / tail_cnt;
+      const int t = (int)xcd_remap(b - it.split * tail_cnt, (uint32_t)tail_cnt);
+      tid = dp_cnt + t;
+      it.tile_part = part + ((int64_t)it.split * tail_cnt + t) * BM * BN;
+    }
+    int tm, tn;
+    tile_coords(tid, tiles_m, tiles_n, group_m, tm, tn);
+    it.m0 = tm * BM;
+    it.n0 = tn * BN;
+    it.m_rows = min(BM, M - it.m0);
+    const int k_begin = it.split * kc;
+    it.K = min(K_total - k_begin, kc);
+    it.xb = (uint64_t)(uintptr_t)(x + (int64_t)it.m0 * ld + k_begin);
+    it.xrec = (uint32_t)(((int64_t)(it.m_rows - 1) * ld + it.K) * 2);
+    it.wb = (uint64_t)(uintptr_t)(W + (int64_t)it.n0 * ld + k_begin);
+    it.wrec = (uint32_t)(((int64_t)(min(BN, N - it.n0) - 1) * ld + it.K) * 2);
+    return it;
+  };
+
+  // This workgroup's chain: items id, id + kNumCUs, ... below id_end (a
+  // launch's items run in rounds of kNumCUs, `chain` rounds per workgroup).
+  int id = (int)(blockIdx.x / kNumCUs) * (kNumCUs * chain) + (int)(blockIdx.x % kNumCUs);
+  const int id_end = min(items, (int)(blockIdx.x / kNumCUs + 1) * (kNumCUs * chain));
+  if (id >= id_end) return;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave % C::WGM, wn = wave / C::WGM;
-  const __amdgpu_buffer_rsrc_t xr =
-      make_rsrc(x + (int64_t)m0 * ld + k_begin, (uint32_t)(((int64_t)(m_rows - 1) * ld + K) * 2));
-  const __amdgpu_buffer_rsrc_t wr =
-      make_rsrc(W + (int64_t)n0 * ld + k_begin, (uint32_t)(((int64_t)(min(BN, N - n0) - 1) * ld + K) * 2));
-  constexpr int LX = BM / C::kRowsPerLoad / C::kWaves, LW = BN / C::kRowsPerLoad / C::kWaves;
-  constexpr int L = LX + LW;
-  static_assert(L * 4 == TM * TN, "one load after every fourth MFMA of a k-step");
+
+  // Byte offsets of the rows this lane loads, its 16-byte chunk swizzled: x by
+  // row mod 8, W by the row's place in its fragment mod 8.
+  const int rl = lane / C::kCPR, pc = lane % C::kCPR;
+  const int xc = pc ^ rl, wc = pc ^ ((rl & 3) | ((wave & 1) << 2));
   uint32_t xro[LX], wro[LW];
 #pragma unroll
-  for (int g = 0; g < LX; ++g) xro[g] = (uint32_t)(((g * C::kWaves + wave) * C::kRowsPerLoad + lane / C::kCPR) * ld * 2);
-#pragma unroll
-  for (int g = 0; g < LW; ++g) wro[g] = (uint32_t)(((g * C::kWaves + wave) * C::kRowsPerLoad + lane / C::kCPR) * ld * 2);
+  for (int g = 0; g < LX; ++g) {
+    const int r = (g * C::kWaves + wave) * C::kRowsPerLoad + rl;
+    xro[g] = (uint32_t)(r * ld * 2) + (uint32_t)(xc << 4);
+    wro[g] = (uint32_t)(r * ld * 2) + (uint32_t)(wc << 4);
+  }
 
   f32x4 acc[TN][TM];
 #pragma unroll
@@ -614,168 +685,267 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
 #pragma unroll
     for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{};
 
-  const int nk = (K + BK - 1) / BK;
-  // The ring holds five half-slices of HB bytes: the lead operand's rows of
-  // slice s (x if XLEAD, else W) are half 2s, the other operand's half 2s + 1,
-  // and half u lives in buffer u mod 5.
+  Item cur = decode(id), nxt;
+  bool has_next = false;
+  // The item the load cursors enter next.  (The cursors are at most two
+  // slices ahead, so an item followed by another has at least three slices;
+  // the launcher sees to it.)
+  auto next_item = [&]() {
+    id += kNumCUs;
+    has_next = id < id_end;
+    if (has_next) {
+      nxt = decode(id);
+    } else {
+      // nothing left: every further load is out of range (zeros into buffers
+      // no wave reads any more)
+      nxt.xb = cur.xb;
+      nxt.wb = cur.wb;
+      nxt.xrec = nxt.wrec = 0;
+      nxt.K = 0x40000000;
+    }
+  };
+  // Load cursors of the lead (l) and the other operand (f): base, records and
+  // k left in the item.  A row past the item's end lies past the records
+  // whatever the k; k past the range (RAGGED_K) is masked per lane.
+  uint64_t lb = XLEAD ? cur.xb : cur.wb, fb = XLEAD ? cur.wb : cur.xb;
+  uint32_t lrec = XLEAD ? cur.xrec : cur.wrec, frec = XLEAD ? cur.wrec : cur.xrec;
+  int lk = cur.K, fk = cur.K;
+  // one slice further, in three parts that each fit between two MFMAs
+  auto advance = [&](auto lead_c, int step) {
+    constexpr bool LEAD = decltype(lead_c)::value, ISX = LEAD == XLEAD;
+    uint64_t& base = LEAD ? lb : fb;
+    uint32_t& rec = LEAD ? lrec : frec;
+    int& kl = LEAD ? lk : fk;
+    if (step == 0) {
+      pin_s(base);
+      base += BK * 2;
+      pin_s(base);
+    } else if (step == 1) {
+      pin_s(kl);
+      kl -= BK;
+      pin_s(kl);
+      base = kl > 0 ? base : (ISX ? nxt.xb : nxt.wb);
+      pin_s(base);
+    } else {
+      pin_s(kl);
+      rec = kl > 0 ? rec : (ISX ? nxt.xrec : nxt.wrec);
+      kl = kl > 0 ? kl : nxt.K;
+      pin_s(rec);
+      pin_s(kl);
+    }
+  };
   constexpr int HB = BM * C::kRowBytes;
-  // load g (0 .. 7) of the x (ISX) or W half of slice s into buffer dst
-  // (zeros past the end)
-  auto load_half = [&](auto isx_c, OPS_LDS char* dst, int s, int g) {
-    constexpr bool ISX = decltype(isx_c)::value;
-    const int rl = lane / C::kCPR, pc = lane % C::kCPR;
-    const int grp = g * C::kWaves + wave;
-    const int r = grp * C::kRowsPerLoad + rl;
-    // (a slice past the end starts at K, so every lane's k is out of range:
-    // one select per load and no branch)
-    const int k = (s < nk ? s * BK : K) + ((pc ^ swz<C::kCPR>(r)) << 3);
-    const uint32_t voff = k < K ? (ISX ? xro[g] : wro[g]) + (uint32_t)k * 2u : kOobOffset;
-    buffer_load16_lds<kNoL1>(ISX ? xr : wr, dst + grp * 1024, voff);
+  // load g (0 .. 7) of the cursor's half-slice into LDS buffer dst
+  auto load_half = [&](auto lead_c, uint32_t dst, int g) {
+    constexpr bool LEAD = decltype(lead_c)::value, ISX = LEAD == XLEAD;
+    uint32_t voff = ISX ? xro[g] : wro[g];
+    if (RAGGED_K) voff = (ISX ? xc : wc) * 8 < (LEAD ? lk : fk) ? voff : kOutOfRange;
+    buffer_load16_lds<kNoL1>(make_rsrc((const void*)(uintptr_t)(LEAD ? lb : fb), LEAD ? lrec : frec),
+                             (OPS_LDS char*)(uintptr_t)(dst + (g * C::kWaves + wave) * 1024), voff);
   };
-  using TL = std::integral_constant<bool, XLEAD>;   // the lead operand (true: x)
-  using TF = std::integral_constant<bool, !XLEAD>;  // the other one
-  const int fr = lane & (MI - 1), fh = lane / MI;
-  int lane_off[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) lane_off[ks] = fr * C::kRowBytes + (((4 * ks + fh) ^ swz<C::kCPR>(fr)) << 4);
-  const int x_row0 = wm * WM * C::kRowBytes, w_row0 = wn * WN * C::kRowBytes;
+  using LD = std::true_type;   // the lead operand
+  using FO = std::false_type;  // the other one
 
+  const int fr = lane & (MI - 1), fh = lane / MI;
+  uint32_t x_off[KS], w_off[KS];  // this lane's fragment row and chunk in k-step ks
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const int ch = ((4 * ks + fh) ^ (fr & 7)) << 4;
+    x_off[ks] = (wm * WM + fr) * C::kRowBytes + ch;
+    w_off[ks] = (wn * WN + (fr >> 2) * 8 + (fr & 3)) * C::kRowBytes + ch;
+  }
   bf16x8 a[2][TN], b[2][TM];
-  // fragment read r (0 .. TN + TM - 1) of a k-step from the x half rx and the
-  // W half rw, in the order the MFMAs (i outer, j inner) first need them:
-  // b0, a0, b1 .. b7, a1 .. a7
-  auto read_frag = [&](const OPS_LDS char* rx, const OPS_LDS char* rw, int ks, int buf, int r) {
-    if (r == 0) b[buf][0] = lds_frag<C>(rx + x_row0 + lane_off[ks]);
-    else if (r == 1) a[buf][0] = lds_frag<C>(rw + w_row0 + lane_off[ks]);
-    else if (r < TM + 1) b[buf][r - 1] = lds_frag<C>(rx + x_row0 + (r - 1) * MI * C::kRowBytes + lane_off[ks]);
-    else a[buf][r - TM] = lds_frag<C>(rw + w_row0 + (r - TM) * MI * C::kRowBytes + lane_off[ks]);
+  uint32_t ax, aw;  // fragment addresses (x, W) of the next reads
+  // fragment read r (0 .. TN + TM - 1) of a k-step, in the order the MFMAs (i
+  // outer, j inner) first need them: b0, a0, b1 .. b7, a1 .. a7
+  auto read_frag = [&](int buf, int r) {
+    auto xf = [&](int j) { return lds_frag<C>((const OPS_LDS char*)(uintptr_t)(ax + j * MI * C::kRowBytes)); };
+    auto wf = [&](int i) {
+      return lds_frag<C>((const OPS_LDS char*)(uintptr_t)(aw + ((i >> 1) * 32 + (i & 1) * 4) * C::kRowBytes));
+    };
+    if (r == 0) b[buf][0] = xf(0);
+    else if (r == 1) a[buf][0] = wf(0);
+    else if (r < TM + 1) b[buf][r - 1] = xf(r - 1);
+    else a[buf][r - TM] = wf(r - TM);
   };
-  // one k-step on fragment buffer buf; READ: the next k-step's fragments
-  // (halves rx / rw, k-step rks) into buf ^ 1; LOAD: the other operand's half
-  // of slice kt + 2 into df, then the lead operand's half of slice kt + 3
-  // into dl (in this order: the next barrier waits for the first and leaves
-  // the second in flight)
-  auto kstep = [&](auto buf_c, auto read_c, auto load_c, const OPS_LDS char* rx, const OPS_LDS char* rw, int rks,
-                   OPS_LDS char* df, OPS_LDS char* dl, int kt) {
+  // One k-step on fragment buffer BUF: the next one's fragments into the
+  // other, the cursor's half-slice into LDS buffer dst, side(q) after MFMA q.
+  // Its own fragments have landed (the LDS counter is cleared before it, so
+  // the compiler needs no wait inside the run; it could not name one that
+  // lets the new reads stay in flight: the counter holds at most 15).
+  auto kstep = [&](auto buf_c, auto lead_c, uint32_t dst, auto side) {
     constexpr int buf = decltype(buf_c)::value;
-    constexpr bool READ = decltype(read_c)::value, LOAD = decltype(load_c)::value;
-    // This k-step's fragments were read one k-step ago and have landed; with
-    // the counter cleared the compiler needs no wait inside the MFMA run (it
-    // could not name one that lets the new reads stay in flight: the LDS
-    // counter holds at most 15).
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt unconstrained
 #pragma unroll
     for (int q = 0; q < TN * TM; ++q) {
       mfma_agpr(acc[q / TM][q % TM], a[buf][q / TM], b[buf][q % TM]);
-      if (READ && q < TN + TM) read_frag(rx, rw, rks, buf ^ 1, q);
-      if (LOAD && (q & 3) == 3) {
-        const int l = q >> 2;
-        if (l < LW) load_half(TF{}, df, kt + 2, l);
-        else load_half(TL{}, dl, kt + 3, l - LW);
-      }
+      if (q % 2 == 0 && q / 2 < TN + TM) read_frag(buf ^ 1, q / 2);
+      if ((q & 7) == 3) load_half(lead_c, dst, q >> 3);
+      side(q);
     }
   };
   using B0 = std::integral_constant<int, 0>;
   using B1 = std::integral_constant<int, 1>;
-  using T = std::true_type;
-  using F = std::false_type;
-  static_assert(KS == 2, "two k-steps per slice");
-  static_assert(BM == BN && LX == 8 && LW == 8, "square tile: x and W halves of 8 loads per wave");
 
-  // prologue: halves 0 .. 4 (slices 0 and 1, the lead half of slice 2)
+  // Ring buffers (LDS addresses): c0 and c1 hold the lead and the other half
+  // of slice s, c2 and c3 those of slice s + 1, c4 the lead half of slice s + 2.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(OPS_LDS char*)smem_raw;
+  uint32_t c0 = lds0, c1 = lds0 + HB, c2 = lds0 + 2 * HB, c3 = lds0 + 3 * HB, c4 = lds0 + 4 * HB;
 #pragma unroll
-  for (int g = 0; g < LX; ++g) load_half(TL{}, smem, 0, g);
+  for (int g = 0; g < LX; ++g) load_half(LD{}, c0, g);
 #pragma unroll
-  for (int g = 0; g < LW; ++g) load_half(TF{}, smem + HB, 0, g);
+  for (int g = 0; g < LX; ++g) load_half(FO{}, c1, g);
+  next_item();
 #pragma unroll
-  for (int g = 0; g < LX; ++g) load_half(TL{}, smem + 2 * HB, 1, g);
+  for (int p = 0; p < 3; ++p) {
+    advance(LD{}, p);
+    advance(FO{}, p);
+  }
 #pragma unroll
-  for (int g = 0; g < LW; ++g) load_half(TF{}, smem + 3 * HB, 1, g);
+  for (int g = 0; g < LX; ++g) load_half(LD{}, c2, g);
 #pragma unroll
-  for (int g = 0; g < LX; ++g) load_half(TL{}, smem + 4 * HB, 2, g);
-  wait_vmcnt<3 * LX>();  // slice 0 has landed (three halves still in flight)
+  for (int g = 0; g < LX; ++g) load_half(FO{}, c3, g);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) advance(LD{}, p);  // (the other cursor moves in the loop's first k-step)
+  wait_vmcnt<2 * LX>();                          // slice 0 has landed
   barrier_keep_loads();
+  ax = x_off[0] + (XLEAD ? c0 : c1);
+  aw = w_off[0] + (XLEAD ? c1 : c0);
 #pragma unroll
-  for (int r = 0; r < TN + TM; ++r) read_frag(XLEAD ? smem : smem + HB, XLEAD ? smem + HB : smem, 0, 0, r);
+  for (int r = 0; r < TN + TM; ++r) read_frag(0, r);
+  ax = x_off[1] + (XLEAD ? c0 : c1);
+  aw = w_off[1] + (XLEAD ? c1 : c0);
   // the accumulators were zeroed by VALU writes: two wait states before an
   // MFMA reads them (the assembler statement hides them from the compiler)
   asm volatile("s_nop 1" ::);
-  int li = 0, fi = 1;  // buffers of slice kt's lead and other halves
-  for (int kt = 0; kt < nk; ++kt) {
-    const int ln = li + 2 < 5 ? li + 2 : li - 3, fn = fi + 2 < 5 ? fi + 2 : fi - 3;  // slice kt + 1
-    OPS_LDS char* sl = smem + li * HB;
-    OPS_LDS char* sf = smem + fi * HB;
-    // Past the last slice the loads read zeros into buffers no wave reads
-    // any more, and the last slice's look-ahead reads fetch fragments that
-    // are never used: one branch-free body keeps every accumulator in one
-    // place.
-    kstep(B0{}, T{}, F{}, XLEAD ? sl : sf, XLEAD ? sf : sl, 1, sl, sf, kt);
-    // slice kt + 1 has landed in every wave (only the lead half of slice
-    // kt + 2 stays in flight) and every wave is done reading slice kt, whose
-    // buffers take the other half of slice kt + 2 (half 2kt + 5) and the lead
-    // half of slice kt + 3 (half 2kt + 6)
-    wait_vmcnt<LX>();
-    barrier_keep_loads();
-    OPS_LDS char* nl = smem + ln * HB;
-    OPS_LDS char* nf = smem + fn * HB;
-    kstep(B1{}, T{}, T{}, XLEAD ? nl : nf, XLEAD ? nf : nl, 0, sl, sf, kt);
-    li = ln;
-    fi = fn;
-  }
-  // The epilogue's reads of the accumulators follow the last MFMA's writes:
-  // a 16-pass XDL write needs up to 19 wait states before another
-  // instruction reads its result.
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::);
-  wait_vmem();
+  int left = (cur.K + BK - 1) / BK;  // slices left of the tile
+  int fresh = 0;                     // 1: the previous tile's stores may be in flight
+  for (;;) {
+    // Past the chain's last slice the same body runs on (loads out of range,
+    // look-ahead reads never used): one branch-free MFMA run keeps every
+    // accumulator in one place.
+    do {
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt unconstrained
+      kstep(B0{}, LD{}, c4, [&](int q) {
+        if (q == 36) advance(FO{}, 0);
+        if (q == 40) advance(FO{}, 1);
+        if (q == 48) advance(FO{}, 2);
+        if (q == 56) {
+          ax = x_off[0] + (XLEAD ? c2 : c3);
+          pin_v(ax);
+        }
+        if (q == 57) {
+          aw = w_off[0] + (XLEAD ? c3 : c2);
+          pin_v(aw);
+        }
+      });
+      // Slice s + 1 has landed in every wave: newer than its loads are the
+      // lead half of slice s + 2 and, in a tile's first slice, the stores of
+      // the tile before it.  And every wave is done reading slice s, whose
+      // buffers take the next loads.
+      if (!fresh) wait_vmcnt<LX>();
+      else wait_vmcnt<LX + kStores>();
+      fresh = 0;
+      barrier_keep_loads();
+      kstep(B1{}, FO{}, c0, [&](int q) {
+        if (q == 36) advance(LD{}, 0);
+        if (q == 40) advance(LD{}, 1);
+        if (q == 48) advance(LD{}, 2);
+        if (q == 56) {
+          ax = x_off[1] + (XLEAD ? c2 : c3);
+          pin_v(ax);
+        }
+        if (q == 57) {
+          aw = w_off[1] + (XLEAD ? c3 : c2);
+          pin_v(aw);
+        }
+        if (q == 60) {
+          const uint32_t t0 = c0, t1 = c1;
+          c0 = c2;
+          c1 = c3;
+          c2 = c4;
+          c3 = t0;
+          c4 = t1;
+          pin_s(c0);
+          pin_s(c1);
+          pin_s(c2);
+        }
+        if (q == 61) {
+          pin_s(c3);
+          pin_s(c4);
+          --left;
+          pin_s(left);
+        }
+      });
+    } while (left > 0);
 
-  if (tile_part) {
+    // The epilogue's reads of the accumulators follow the last MFMA's writes:
+    // a 16-pass XDL write needs up to 19 wait states before another
+    // instruction reads its result.
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::);
+    // (the lane is made opaque: hoisted out of the item loop, the store
+    // addresses would not fit beside the fragments)
+    int elane = lane;
+    pin_v(elane);
+    const int er = elane & (MI - 1), eh = elane / MI;
+    if (part && (tail_cnt == 0 || cur.tile_part)) {
+      // fp32 partials: the compact tile of a split tail, or this K range's rows
+      float* pb = cur.tile_part ? cur.tile_part : part + ((int64_t)cur.split * M + cur.m0) * N + cur.n0;
+      const int64_t pld = cur.tile_part ? BN : N;
+      const int rows = cur.tile_part ? BM : cur.m_rows, cols = cur.tile_part ? BN : N - cur.n0;
 #pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int r = wm * WM + j * MI + fr;
+      for (int j = 0; j < TM; ++j) {
+        const int r = wm * WM + j * MI + er;
 #pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int c = wn * WN + i * MI + fh * 4;
-        *reinterpret_cast<f32x4*>(tile_part + r * BN + c) = agpr_read(acc[i][j]);
+        for (int i = 0; i < TN; ++i) {
+          const int c = wn * WN + (i >> 1) * 32 + eh * 8 + (i & 1) * 4;
+          const f32x4 v = agpr_read(acc[i][j]);
+          if (r < rows && c < cols) *reinterpret_cast<f32x4*>(pb + r * pld + c) = v;
+        }
       }
-    }
-    return;
-  }
-  if (part && tail_cnt == 0) {
-    float* pbase = part + (int64_t)split * M * N;
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int m = m0 + wm * WM + j * MI + fr;
-      if (m - m0 >= m_rows) continue;
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int n = n0 + wn * WN + i * MI + fh * 4;
-        if (n >= N) continue;
-        *reinterpret_cast<f32x4*>(pbase + (int64_t)m * N + n) = agpr_read(acc[i][j]);
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int m = m0 + wm * WM + j * MI + fr;
-    if (m - m0 >= m_rows) continue;
-    __bf16* yrow = y + (int64_t)m * N;
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      const int n = n0 + wn * WN + i * MI + fh * 4;
-      if (n >= N) continue;
-      const f32x4 v = agpr_read(acc[i][j]);
-      float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+    } else {
+      // exactly kStores stores per wave, whatever the tile's edges (out of
+      // range ones are dropped): the wait above counts them
+      fresh = 1;
+      const __amdgpu_buffer_rsrc_t yr = make_rsrc(
+          y + (int64_t)cur.m0 * N + cur.n0, (uint32_t)(((int64_t)(cur.m_rows - 1) * N + N - cur.n0) * 2));
+      const int c0e = wn * WN + eh * 8;
+      u32x4 bb[TN / 2] = {};
       if (bias) {
-        const u32x2 bb = *reinterpret_cast<const u32x2*>(bias + n);
-        v0 += bf_lo(bb[0]);
-        v1 += bf_hi(bb[0]);
-        v2 += bf_lo(bb[1]);
-        v3 += bf_hi(bb[1]);
+#pragma unroll
+        for (int p = 0; p < TN / 2; ++p)
+          if (cur.n0 + c0e + p * 32 < N) bb[p] = *reinterpret_cast<const u32x4*>(bias + cur.n0 + c0e + p * 32);
       }
-      *reinterpret_cast<u32x2*>(yrow + n) = u32x2{pack_bf2(v0, v1), pack_bf2(v2, v3)};
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const int r = wm * WM + j * MI + er;
+        const uint32_t row = (uint32_t)(r * N + c0e) * 2u;
+#pragma unroll
+        for (int p = 0; p < TN / 2; ++p) {
+          f32x4 lo = agpr_read(acc[2 * p][j]), hi = agpr_read(acc[2 * p + 1][j]);
+          if (bias) {
+            lo += f32x4{bf_lo(bb[p][0]), bf_hi(bb[p][0]), bf_lo(bb[p][1]), bf_hi(bb[p][1])};
+            hi += f32x4{bf_lo(bb[p][2]), bf_hi(bb[p][2]), bf_lo(bb[p][3]), bf_hi(bb[p][3])};
+          }
+          const uint32_t off = r < cur.m_rows && cur.n0 + c0e + p * 32 < N ? row + p * 64 : kOutOfRange;
+          __builtin_amdgcn_raw_buffer_store_b128(
+              u32x4{pack_bf2(lo[0], lo[1]), pack_bf2(lo[2], lo[3]), pack_bf2(hi[0], hi[1]), pack_bf2(hi[2], hi[3])}, yr,
+              off, 0, 0);
+        }
+      }
     }
+    if (!has_next) break;
+    u32x2 zero = {0u, 0u};
+    pin_v(zero);
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) agpr_zero(acc[i][j], zero);
+    cur = nxt;
+    left = (cur.K + BK - 1) / BK;
+    next_item();
+    asm volatile("s_nop 7" ::);  // (the last zeroes are written before an MFMA reads them)
   }
+  wait_vmem();  // no LDS DMA may still be in flight when the workgroup ends
 }
 
 // ------------------------------------------------------------ fp32 path ----
@@ -907,49 +1077,25 @@ static int split_ranges(int64_t K, int splits, int BK) {
 // the last, partly filled round run split (compact fp32 partial tiles in
 // `part`), the other tiles as usual in the same launch.  `part` is the
 // caller's workspace, sized by plan_linear.
-template <class C, bool XLEAD>
-static constexpr auto gemm_kernel() {
-  if constexpr (std::is_same<C, CfgW4>::value) return &gemm_bf16_w4_kernel<C, XLEAD>;
-  else return &gemm_bf16_kernel<C, false>;
-}
-
-// Dynamic LDS of a launch: the four-wave kernel's ring is five half-slices
-// (x or W rows of one slice each), the others STAGES whole slices.
-template <class C>
-static constexpr int gemm_lds_bytes() {
-  if constexpr (std::is_same<C, CfgW4>::value) return 5 * C::BM * C::kRowBytes;
-  else return C::kLdsBytes;
-}
-
 template <class C>
 static hipError_t launch_gemm_bf16(const void* x, const void* W, const void* bias, void* y, int64_t M,
                                    int64_t N, int64_t K, hipStream_t s, int splits, int tail_splits, float* part) {
   // More than 64 KB of dynamic LDS per workgroup needs the limit raised once
   // per process (a host-side function attribute, no allocation).
-  static const hipError_t attr = [] {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<C, true>()),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<C>());
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<C, false>()),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<C>());
-  }();
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<C, false>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
   if (attr != hipSuccess) return attr;
   const int64_t tiles_m = (M + C::BM - 1) / C::BM;
   const int64_t tiles_n = (N + C::BN - 1) / C::BN;
   const int64_t tiles = tiles_m * tiles_n;
   const int group_m = tile_group_rows<C>(tiles_m, tiles_n, K);
-  // The four-wave kernel's ring gives two slices of lead to one operand: the
-  // one with fewer distinct blocks among the 32 tiles an XCD runs at once (x
-  // when a group spans at most 4 tile-rows, i.e. K >= 8192; W for the 8-row
-  // groups of K = 4096).  Same-box, flushed: the 8B gate-up 1579 -> 1526 us
-  // with W leading, down 769 -> 752 us and the 70B gate-up and down 3-4 %
-  // faster with x leading.
-  const auto kern = group_m <= 4 ? gemm_kernel<C, true>() : gemm_kernel<C, false>();
+  const auto kern = &gemm_bf16_kernel<C, false>;
   if (tail_splits > 1) {
     const int64_t tail = tiles % kNumCUs, dp = tiles - tail;
     const int64_t kchunk = split_chunk(K, tail_splits, C::BK);
     const int nsplit = split_ranges(K, tail_splits, C::BK);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(dp + tail * nsplit)), dim3(C::kThreads), gemm_lds_bytes<C>(),
+    hipLaunchKernelGGL(kern, dim3((unsigned)(dp + tail * nsplit)), dim3(C::kThreads), C::kLdsBytes,
                        s, static_cast<const __bf16*>(x), static_cast<const __bf16*>(W),
                        static_cast<const __bf16*>(bias), static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m,
                        (int)kchunk, part, GroupedGemm{}, (int)dp, (int)tail);
@@ -963,13 +1109,70 @@ static hipError_t launch_gemm_bf16(const void* x, const void* W, const void* bia
   const bool split = splits > 1;
   const int64_t kchunk = split ? split_chunk(K, splits, C::BK) : K;
   const int nsplit = split ? split_ranges(K, splits, C::BK) : 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(C::kThreads), gemm_lds_bytes<C>(), s,
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(C::kThreads), C::kLdsBytes, s,
                      static_cast<const __bf16*>(x), static_cast<const __bf16*>(W),
                      static_cast<const __bf16*>(bias), static_cast<__bf16*>(y), (int)M, (int)N, (int)K,
                      group_m, (int)kchunk, split ? part : nullptr, GroupedGemm{}, 0, 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !split) return e;
   return launch_splitk_reduce(part, nsplit, bias, y, M, N, s);
+}
+
+// The same launches on the four-wave kernel: items (tiles, then the K ranges
+// of a split tail, or the ranges of every tile) in rounds of kNumCUs, kChain
+// rounds per workgroup.
+template <bool XLEAD, bool RAGGED_K>
+static hipError_t launch_gemm_w4_kernel(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
+                                        int64_t K, int group_m, int64_t kchunk, float* part, int64_t dp, int64_t tail,
+                                        int64_t items, int chain, hipStream_t s) {
+  using C = CfgW4;
+  constexpr int kLds = 5 * C::BM * C::kRowBytes;  // five half-slices
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  const int64_t per = (int64_t)kNumCUs * chain, full = items / per;
+  const int64_t grid = full * kNumCUs + std::min<int64_t>(kNumCUs, items - full * per);
+  hipLaunchKernelGGL((gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K>), dim3((unsigned)grid), dim3(C::kThreads), kLds, s,
+                     static_cast<const __bf16*>(x), static_cast<const __bf16*>(W), static_cast<const __bf16*>(bias),
+                     static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m, (int)kchunk, part, (int)dp, (int)tail,
+                     (int)items, chain);
+  return hipGetLastError();
+}
+
+static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
+                                 int64_t K, hipStream_t s, int splits, int tail_splits, float* part) {
+  using C = CfgW4;
+  const int64_t tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN, tiles = tiles_m * tiles_n;
+  const int group_m = tile_group_rows<C>(tiles_m, tiles_n, K);
+  const int64_t tail = tail_splits > 1 ? tiles % kNumCUs : 0, dp = tiles - tail;
+  const int sp = tail ? tail_splits : std::max(1, splits);
+  const int64_t kchunk = sp > 1 ? split_chunk(K, sp, C::BK) : K;
+  const int nsplit = sp > 1 ? split_ranges(K, sp, C::BK) : 1;
+  const int64_t items = tail ? dp + tail * nsplit : tiles * nsplit;
+  // the kernel's load cursors run two slices ahead, into the next item only:
+  // items of fewer than three slices are not chained
+  const int chain = K - (nsplit - 1) * kchunk > 2 * C::BK ? kChain : 1;
+  // The ring gives half a slice more of lead to one operand: the one with
+  // fewer distinct blocks among the 32 tiles an XCD runs at once (x when a
+  // group spans at most 4 tile-rows, i.e. K >= 8192; W for the 8-row groups of
+  // K = 4096).  Same-box, flushed, measured on the ring's first form: the 8B
+  // gate-up 1579 -> 1526 us with W leading, down 769 -> 752 us and the 70B
+  // gate-up and down 3-4 % faster with x leading.
+  const bool xlead = group_m <= 4, ragged = K % C::BK != 0;
+  const auto go = [&](auto xl, auto rk) {
+    return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value>(
+        x, W, bias, y, M, N, K, group_m, kchunk, sp > 1 ? part : nullptr, tail ? dp : 0, tail, items, chain, s);
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  const hipError_t e = xlead ? (ragged ? go(T{}, T{}) : go(T{}, F{})) : (ragged ? go(F{}, T{}) : go(F{}, F{}));
+  if (e != hipSuccess || sp == 1) return e;
+  if (!tail) return launch_splitk_reduce(part, nsplit, bias, y, M, N, s);
+  hipLaunchKernelGGL((splitk_tile_reduce_kernel<C::BM, C::BN>), dim3((unsigned)tail, C::BM / 16), dim3(256), 0, s,
+                     static_cast<const float*>(part), nsplit, (int)dp, (int)tail, (int)M, (int)N, (int)tiles_m,
+                     (int)tiles_n, group_m, static_cast<const __bf16*>(bias), static_cast<__bf16*>(y));
+  return hipGetLastError();
 }
 
 hipError_t launch_splitk_reduce(const float* part, int splits, const void* bias, void* y, int64_t M, int64_t N,
@@ -1091,7 +1294,7 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
       const int s_wide = splitk_count<CfgBig8>(M, N, K), s_mid = splitk_count<CfgMid>(M, N, K);
       const int64_t w_wide = (int64_t)s_wide * ((N + 255) / 256), w_mid = (int64_t)s_mid * ((N + 127) / 128);
       if (w_wide >= w_mid && s_wide > 1) {
-        p.cfg = kCfgW4; p.splits = s_wide; p.ws_bytes = split_bytes<CfgW4>(M, N, K, s_wide); return p;
+        p.cfg = N < kW4MaxN ? kCfgW4 : kCfgBig8; p.splits = s_wide; p.ws_bytes = split_bytes<CfgW4>(M, N, K, s_wide); return p;
       }
       if (s_mid > 1) { p.cfg = kCfgMid; p.splits = s_mid; p.ws_bytes = split_bytes<CfgMid>(M, N, K, s_mid); return p; }
     }
@@ -1136,7 +1339,7 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
       if (c == 0 || t < best_t) { best = c; best_t = t; }
     }
   }
-  p.cfg = best == 0 ? (force_tile == 3 ? kCfgBig8 : kCfgW4) : best == 1 ? kCfgT192 : kCfgMid;
+  p.cfg = best == 0 ? (force_tile == 3 || N >= kW4MaxN ? kCfgBig8 : kCfgW4) : best == 1 ? kCfgT192 : kCfgMid;
   p.tail_splits = tail_splits(((M + choices[best].bm - 1) / choices[best].bm) *
                               ((N + choices[best].bn - 1) / choices[best].bn));
   if (p.tail_splits > 1)
@@ -1157,7 +1360,7 @@ hipError_t launch_linear(const LinearPlan& p, const void* x, const void* W, cons
     case LinearPlan::kTiled:
       switch (p.cfg) {
         case kCfgBig8: return launch_gemm_bf16<CfgBig8>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
-        case kCfgW4: return launch_gemm_bf16<CfgW4>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
+        case kCfgW4: return launch_gemm_w4(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
         case kCfgT192: return launch_gemm_bf16<CfgT192>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
         case kCfgMid: return launch_gemm_bf16<CfgMid>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
         case kCfgSk64: return launch_gemm_bf16<CfgSk64>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);

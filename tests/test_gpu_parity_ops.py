@@ -209,6 +209,34 @@ def test_linear_four_and_eight_waves_agree(ops, tune, M, N, K, bias):
     assert_close(f64(y4.cpu()), oracle.linear(f64(x), f64(W), None if b is None else f64(b)), "bf16", "linear")
 
 
+@pytest.mark.parametrize("M,N,K,bias", [(4300, 8200, 192, True), (4300, 8200, 136, False), (4300, 8200, 128, True),
+                                        (9000, 8456, 320, True), (5200, 5000, 1032, True)])
+def test_linear_chained_tiles(ops, tune, M, N, K, bias):
+    """More 256x256 tiles than one round of the CUs: a workgroup of the
+    four-wave kernel runs a chain of them (561 to 1224 tiles: chains of three
+    and four, the last one ragged), the next tile's first slices loading while
+    the previous one ends.  K of three slices (the fewest chained), of two
+    and a part, of two (not chained: each tile a workgroup), of five, of
+    sixteen and a part; a split tail at the end of a chain; ragged M and N.  Bitwise
+    equal to the eight-wave kernel, which runs one tile per workgroup."""
+    import torch
+    say(f"linear bf16 chained tiles M={M} N={N} K={K} bias={bias}")
+    x = gen(29, "x", (M, K), "bf16")
+    W = gen(29, "w_qkv", (N, K), "bf16", std=0.02)
+    b = gen(29, "bias", (N,), "bf16") if bias else None
+    args = (cuda(x), cuda(W), None if b is None else cuda(b))
+    got = []
+    for tile in ("256x256", "256x256", "256x256w8"):
+        tune(gemm_tile=TILES[tile])
+        got.append(ops.opscale_linear(*args))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+    assert torch.equal(got[0].view(torch.int16), got[2].view(torch.int16))
+    rows = np.unique(np.r_[0:M:97, 255:M:256, M - 1])
+    ref = oracle.linear(f64(x[rows]), f64(W), None if b is None else f64(b))
+    assert_close(f64(got[0].cpu()[rows]), ref, "bf16", "linear chained")
+
+
 @pytest.mark.parametrize("tile,M,N,K,bias", [("256x256", 4352, 4096, 1024, True), ("256x256", 4300, 4104, 2056, False),
                                              ("192x256", 4352, 4096, 1024, False),
                                              ("256x256w8", 4300, 4104, 2056, True)])
