@@ -78,6 +78,21 @@ def test_fused_moe(ops, tune, fuse, T, H, F, E, k):
     assert_close(got, ref, "bf16", "fused_moe")
 
 
+@pytest.mark.parametrize("T,E,k", [(512, 8, 2), (513, 256, 2), (31, 1, 1), (90, 257, 4), (4096, 5, 2), (4097, 5, 2)])
+def test_fused_moe_sort_sizes(ops, T, E, k):
+    """The sort at its edges: lists of exactly and just past a whole wave of
+    entries for each of its 16 waves, the most experts and entries of the
+    one-workgroup form (256; 8192) and one more of each (three kernels), one
+    expert; invalid ids among them."""
+    say(f"fused_moe sort T={T} E={E} topk={k}")
+    rng = np.random.default_rng(T + E)
+    ids = rng.integers(0, E, size=(T, k))
+    ids[::97, 0] = -1
+    ids[5::131, k - 1] = E
+    got, ref = _moe_case(ops, T, 32, 16, E, k, seed=T + E, ids=ids)
+    assert_close(got, ref, "bf16", "fused_moe sort sizes")
+
+
 def test_fused_moe_one_hot_expert(ops):
     """Every token to expert 2 (600 rows: three 256-row tiles), the others empty."""
     say("fused_moe all tokens to one expert")
