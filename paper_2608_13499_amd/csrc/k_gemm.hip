@@ -6,8 +6,9 @@
 // are fetched with buffer_load ... lds (HBM/L2 -> LDS without passing through
 // registers) while the current one feeds the matrix cores.  Large problems
 // use four waves of 128x128 sub-tiles, one per SIMD, with the accumulators in
-// AGPRs (gemm_bf16_w4_kernel); the eight-wave form of the same tile (two waves
-// of 128x64 per SIMD) serves the grouped mixture-of-experts GEMMs.  Problems
+// AGPRs (gemm_bf16_w4_kernel), the grouped mixture-of-experts GEMMs among them;
+// the eight-wave form of the same tile (two waves of 128x64 per SIMD) takes
+// what that kernel's chains and 32-bit offsets do not.  Problems
 // whose last round of 256x256 tiles would be mostly idle take 192x256 or
 // 256x128 tiles; decode-sized M splits K.  Rows
 // and K columns beyond the matrix read as zeros through the buffer
@@ -594,14 +595,15 @@ __device__ __forceinline__ void pin_v(V& v) {
 // two accumulators hold eight consecutive columns: one 16-byte store.  The W
 // rows are swizzled by that row's place in the fragment, as the x rows are.
 constexpr int kChain = 4;
-template <class C, bool XLEAD, bool RAGGED_K>
+template <class C, bool XLEAD, bool RAGGED_K, bool GROUPED>
 __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf16* __restrict__ x,
                                                                       const __bf16* __restrict__ W,
                                                                       const __bf16* __restrict__ bias,
                                                                       __bf16* __restrict__ y, int M, int N,
                                                                       int K_total, int group_m, int kchunk,
-                                                                      float* __restrict__ part, int dp_cnt,
-                                                                      int tail_cnt, int items, int chain) {
+                                                                      float* __restrict__ part, GroupedGemm gg,
+                                                                      int dp_cnt, int tail_cnt, int items,
+                                                                      int chain) {
   static_assert(C::kWaves == 4 && C::WM == 128 && C::WN == 128 && !C::DEEP, "four waves of 128x128");
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, WM = C::WM, WN = C::WN;
@@ -616,6 +618,8 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
   const int tiles_m = (M + BM - 1) / BM;
   const int tiles = tiles_m * tiles_n;
   const int ld = K_total;
+  const bool fused = GROUPED && gg.swiglu_f > 0;
+  if constexpr (GROUPED) items = gg.tiles[gg.E] * tiles_n;  // (the grid is an upper bound)
 
   // One work item: a tile and its K range.
   struct Item {
@@ -630,6 +634,31 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
     it.split = 0;
     it.tile_part = nullptr;
     int kc = kchunk;
+    if constexpr (GROUPED) {
+      // items in the order expert, column block, tile-row of the expert
+      const int l = (int)xcd_remap((uint32_t)id, (uint32_t)items);
+      int lo = 0, hi = gg.E;  // gg.tiles[lo] * tiles_n <= l < gg.tiles[hi] * tiles_n
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (gg.tiles[mid] * tiles_n <= l) lo = mid;
+        else hi = mid;
+      }
+      const int t0 = gg.tiles[lo], tr_e = gg.tiles[lo + 1] - t0;  // tile-rows of expert lo (>= 1)
+      const int local = l - t0 * tiles_n;
+      const int tn = local / tr_e, tr = local - tn * tr_e;
+      it.n0 = tn * BN;
+      it.m0 = gg.rows[lo] + tr * BM;
+      it.m_rows = min(BM, gg.rows[lo + 1] - it.m0);
+      it.K = ld;
+      // x: the whole operand (rows are gathered per lane); W: the expert's
+      // rows from the tile's first (fused SwiGLU: gate row n0 / 2) on
+      it.xb = (uint64_t)(uintptr_t)x;
+      it.xrec = (uint32_t)((int64_t)gg.x_rows * ld * 2);
+      const int w0 = fused ? it.n0 / 2 : it.n0;
+      it.wb = (uint64_t)(uintptr_t)(W + lo * gg.w_stride + (int64_t)w0 * ld);
+      it.wrec = (uint32_t)((int64_t)(fused ? N - w0 : min(BN, N - it.n0)) * ld * 2);
+      return it;
+    }
     uint32_t tid;
     if (tail_cnt == 0) {
       it.split = id / tiles;
@@ -672,12 +701,29 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
   const int rl = lane / C::kCPR, pc = lane % C::kCPR;
   const int xc = pc ^ rl, wc = pc ^ ((rl & 3) | ((wave & 1) << 2));
   uint32_t xro[LX], wro[LW];
+  auto load_row = [&](int g) { return (g * C::kWaves + wave) * C::kRowsPerLoad + rl; };
 #pragma unroll
   for (int g = 0; g < LX; ++g) {
-    const int r = (g * C::kWaves + wave) * C::kRowsPerLoad + rl;
+    const int r = load_row(g);
     xro[g] = (uint32_t)(r * ld * 2) + (uint32_t)(xc << 4);
-    wro[g] = (uint32_t)(r * ld * 2) + (uint32_t)(wc << 4);
+    // (fused SwiGLU: column c is gate row c / 2, or up row F + c / 2 if odd)
+    wro[g] = (uint32_t)((int64_t)(fused ? (r & 1) * gg.swiglu_f + (r >> 1) : r) * ld * 2) + (uint32_t)(wc << 4);
   }
+  // Grouped: the x rows of an item's tile (-1: none), and their offsets.
+  auto gather_rows = [&](const Item& it, int (&src)[LX]) {
+#pragma unroll
+    for (int g = 0; g < LX; ++g) {
+      const int r = load_row(g);
+      src[g] = -1;
+      if (r < it.m_rows) src[g] = gg.gather ? gg.gather[it.m0 + r] : it.m0 + r;
+    }
+  };
+  auto row_offsets = [&](const int (&src)[LX], uint32_t (&off)[LX]) {
+#pragma unroll
+    for (int g = 0; g < LX; ++g)
+      off[g] = src[g] >= 0 ? (uint32_t)((int64_t)src[g] * ld * 2) + (uint32_t)(xc << 4) : kOutOfRange;
+  };
+  [[maybe_unused]] uint32_t xnext[LX] = {};  // grouped: offsets of the item the x cursor enters next
 
   f32x4 acc[TN][TM];
 #pragma unroll
@@ -686,6 +732,11 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
     for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{};
 
   Item cur = decode(id), nxt;
+  if constexpr (GROUPED) {
+    int src[LX];
+    gather_rows(cur, src);
+    row_offsets(src, xro);
+  }
   bool has_next = false;
   // The item the load cursors enter next.  (The cursors are at most two
   // slices ahead, so an item followed by another has at least three slices;
@@ -710,7 +761,9 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
   uint64_t lb = XLEAD ? cur.xb : cur.wb, fb = XLEAD ? cur.wb : cur.xb;
   uint32_t lrec = XLEAD ? cur.xrec : cur.wrec, frec = XLEAD ? cur.wrec : cur.xrec;
   int lk = cur.K, fk = cur.K;
-  // one slice further, in three parts that each fit between two MFMAs
+  // one slice further, in parts that each fit between two MFMAs
+  constexpr int kAdvance = GROUPED ? 3 + LX / 2 : 3;
+  [[maybe_unused]] int x_moved = 0;  // grouped: the x cursor entered its next item
   auto advance = [&](auto lead_c, int step) {
     constexpr bool LEAD = decltype(lead_c)::value, ISX = LEAD == XLEAD;
     uint64_t& base = LEAD ? lb : fb;
@@ -726,12 +779,20 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
       pin_s(kl);
       base = kl > 0 ? base : (ISX ? nxt.xb : nxt.wb);
       pin_s(base);
-    } else {
+    } else if (step == 2) {
       pin_s(kl);
+      if constexpr (GROUPED && ISX) x_moved = kl > 0 ? 0 : 1;
       rec = kl > 0 ? rec : (ISX ? nxt.xrec : nxt.wrec);
       kl = kl > 0 ? kl : nxt.K;
       pin_s(rec);
       pin_s(kl);
+    } else if constexpr (GROUPED && ISX) {
+#pragma unroll
+      for (int g = 2 * (step - 3); g < 2 * (step - 3) + 2; ++g) {
+        pin_v(xro[g]);
+        xro[g] = x_moved ? xnext[g] : xro[g];
+        pin_v(xro[g]);
+      }
     }
   };
   constexpr int HB = BM * C::kRowBytes;
@@ -795,8 +856,15 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
 #pragma unroll
   for (int g = 0; g < LX; ++g) load_half(FO{}, c1, g);
   next_item();
+  if constexpr (GROUPED) {
+    if (has_next) {
+      int src[LX];
+      gather_rows(nxt, src);
+      row_offsets(src, xnext);
+    }
+  }
 #pragma unroll
-  for (int p = 0; p < 3; ++p) {
+  for (int p = 0; p < kAdvance; ++p) {
     advance(LD{}, p);
     advance(FO{}, p);
   }
@@ -805,7 +873,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
 #pragma unroll
   for (int g = 0; g < LX; ++g) load_half(FO{}, c3, g);
 #pragma unroll
-  for (int p = 0; p < 3; ++p) advance(LD{}, p);  // (the other cursor moves in the loop's first k-step)
+  for (int p = 0; p < kAdvance; ++p) advance(LD{}, p);  // (the other cursor moves in the loop's first k-step)
   wait_vmcnt<2 * LX>();                          // slice 0 has landed
   barrier_keep_loads();
   ax = x_off[0] + (XLEAD ? c0 : c1);
@@ -829,6 +897,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
         if (q == 36) advance(FO{}, 0);
         if (q == 40) advance(FO{}, 1);
         if (q == 48) advance(FO{}, 2);
+        if (q > 48 && q < 46 + kAdvance) advance(FO{}, q - 46);
         if (q == 56) {
           ax = x_off[0] + (XLEAD ? c2 : c3);
           pin_v(ax);
@@ -850,6 +919,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
         if (q == 36) advance(LD{}, 0);
         if (q == 40) advance(LD{}, 1);
         if (q == 48) advance(LD{}, 2);
+        if (q > 48 && q < 46 + kAdvance) advance(LD{}, q - 46);
         if (q == 56) {
           ax = x_off[1] + (XLEAD ? c2 : c3);
           pin_v(ax);
@@ -887,11 +957,22 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
     int elane = lane;
     pin_v(elane);
     const int er = elane & (MI - 1), eh = elane / MI;
-    if (part && (tail_cnt == 0 || cur.tile_part)) {
+    // the item after next, its gathered rows requested before the stores
+    const bool more = has_next;
+    const Item done = cur;
+    if (more) {
+      cur = nxt;
+      next_item();
+    }
+    [[maybe_unused]] int src[LX];
+    if constexpr (GROUPED) {
+      if (more && has_next) gather_rows(nxt, src);
+    }
+    if (!GROUPED && part && (tail_cnt == 0 || done.tile_part)) {
       // fp32 partials: the compact tile of a split tail, or this K range's rows
-      float* pb = cur.tile_part ? cur.tile_part : part + ((int64_t)cur.split * M + cur.m0) * N + cur.n0;
-      const int64_t pld = cur.tile_part ? BN : N;
-      const int rows = cur.tile_part ? BM : cur.m_rows, cols = cur.tile_part ? BN : N - cur.n0;
+      float* pb = done.tile_part ? done.tile_part : part + ((int64_t)done.split * M + done.m0) * N + done.n0;
+      const int64_t pld = done.tile_part ? BN : N;
+      const int rows = done.tile_part ? BM : done.m_rows, cols = done.tile_part ? BN : N - done.n0;
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int r = wm * WM + j * MI + er;
@@ -906,43 +987,54 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
       // exactly kStores stores per wave, whatever the tile's edges (out of
       // range ones are dropped): the wait above counts them
       fresh = 1;
-      const __amdgpu_buffer_rsrc_t yr = make_rsrc(
-          y + (int64_t)cur.m0 * N + cur.n0, (uint32_t)(((int64_t)(cur.m_rows - 1) * N + N - cur.n0) * 2));
+      const int half = fused ? 1 : 0;  // fused SwiGLU: two columns make one activation
+      const int ny = N >> half;
+      const __amdgpu_buffer_rsrc_t yr =
+          make_rsrc(y + (int64_t)done.m0 * ny + (done.n0 >> half),
+                    (uint32_t)(((int64_t)(done.m_rows - 1) * ny + ny - (done.n0 >> half)) * 2));
       const int c0e = wn * WN + eh * 8;
       u32x4 bb[TN / 2] = {};
-      if (bias) {
+      if (!GROUPED && bias) {
 #pragma unroll
         for (int p = 0; p < TN / 2; ++p)
-          if (cur.n0 + c0e + p * 32 < N) bb[p] = *reinterpret_cast<const u32x4*>(bias + cur.n0 + c0e + p * 32);
+          if (done.n0 + c0e + p * 32 < N) bb[p] = *reinterpret_cast<const u32x4*>(bias + done.n0 + c0e + p * 32);
       }
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int r = wm * WM + j * MI + er;
-        const uint32_t row = (uint32_t)(r * N + c0e) * 2u;
+        const uint32_t row = (uint32_t)(r * ny + (c0e >> half)) * 2u;
 #pragma unroll
         for (int p = 0; p < TN / 2; ++p) {
           f32x4 lo = agpr_read(acc[2 * p][j]), hi = agpr_read(acc[2 * p + 1][j]);
-          if (bias) {
+          if (!GROUPED && bias) {
             lo += f32x4{bf_lo(bb[p][0]), bf_hi(bb[p][0]), bf_lo(bb[p][1]), bf_hi(bb[p][1])};
             hi += f32x4{bf_lo(bb[p][2]), bf_hi(bb[p][2]), bf_lo(bb[p][3]), bf_hi(bb[p][3])};
           }
-          const uint32_t off = r < cur.m_rows && cur.n0 + c0e + p * 32 < N ? row + p * 64 : kOutOfRange;
-          __builtin_amdgcn_raw_buffer_store_b128(
-              u32x4{pack_bf2(lo[0], lo[1]), pack_bf2(lo[2], lo[3]), pack_bf2(hi[0], hi[1]), pack_bf2(hi[2], hi[3])}, yr,
-              off, 0, 0);
+          const uint32_t off = r < done.m_rows && done.n0 + c0e + p * 32 < N ? row + (p * 64 >> half) : kOutOfRange;
+          if (fused) {
+            auto act = [](float g, float u) { return g / (1.f + __expf(-g)) * u; };
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf2(act(lo[0], lo[1]), act(lo[2], lo[3])),
+                                                        pack_bf2(act(hi[0], hi[1]), act(hi[2], hi[3]))},
+                                                  yr, off, 0, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b128(
+                u32x4{pack_bf2(lo[0], lo[1]), pack_bf2(lo[2], lo[3]), pack_bf2(hi[0], hi[1]), pack_bf2(hi[2], hi[3])},
+                yr, off, 0, 0);
+          }
         }
       }
     }
-    if (!has_next) break;
+    if (!more) break;
+    if constexpr (GROUPED) {
+      if (has_next) row_offsets(src, xnext);
+    }
     u32x2 zero = {0u, 0u};
     pin_v(zero);
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
       for (int j = 0; j < TM; ++j) agpr_zero(acc[i][j], zero);
-    cur = nxt;
     left = (cur.K + BK - 1) / BK;
-    next_item();
     asm volatile("s_nop 7" ::);  // (the last zeroes are written before an MFMA reads them)
   }
   wait_vmem();  // no LDS DMA may still be in flight when the workgroup ends
@@ -1121,22 +1213,22 @@ static hipError_t launch_gemm_bf16(const void* x, const void* W, const void* bia
 // The same launches on the four-wave kernel: items (tiles, then the K ranges
 // of a split tail, or the ranges of every tile) in rounds of kNumCUs, kChain
 // rounds per workgroup.
-template <bool XLEAD, bool RAGGED_K>
+template <bool XLEAD, bool RAGGED_K, bool GROUPED>
 static hipError_t launch_gemm_w4_kernel(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
                                         int64_t K, int group_m, int64_t kchunk, float* part, int64_t dp, int64_t tail,
-                                        int64_t items, int chain, hipStream_t s) {
+                                        int64_t items, int chain, const GroupedGemm& gg, hipStream_t s) {
   using C = CfgW4;
   constexpr int kLds = 5 * C::BM * C::kRowBytes;  // five half-slices
   static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K, GROUPED>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   const int64_t per = (int64_t)kNumCUs * chain, full = items / per;
   const int64_t grid = full * kNumCUs + std::min<int64_t>(kNumCUs, items - full * per);
-  hipLaunchKernelGGL((gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K>), dim3((unsigned)grid), dim3(C::kThreads), kLds, s,
+  hipLaunchKernelGGL((gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K, GROUPED>), dim3((unsigned)grid), dim3(C::kThreads), kLds, s,
                      static_cast<const __bf16*>(x), static_cast<const __bf16*>(W), static_cast<const __bf16*>(bias),
-                     static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m, (int)kchunk, part, (int)dp, (int)tail,
-                     (int)items, chain);
+                     static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m, (int)kchunk, part, gg, (int)dp,
+                     (int)tail, (int)items, chain);
   return hipGetLastError();
 }
 
@@ -1161,8 +1253,9 @@ static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias,
   // gate-up and down 3-4 % faster with x leading.
   const bool xlead = group_m <= 4, ragged = K % C::BK != 0;
   const auto go = [&](auto xl, auto rk) {
-    return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value>(
-        x, W, bias, y, M, N, K, group_m, kchunk, sp > 1 ? part : nullptr, tail ? dp : 0, tail, items, chain, s);
+    return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value, false>(
+        x, W, bias, y, M, N, K, group_m, kchunk, sp > 1 ? part : nullptr, tail ? dp : 0, tail, items, chain,
+        GroupedGemm{}, s);
   };
   using T = std::true_type;
   using F = std::false_type;
@@ -1226,6 +1319,24 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
                                hipStream_t s) {
   if (tile_rows == CfgRow64::BM)
     return launch_grouped<CfgRow64>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f, s);
+  // Large batches: the four-wave kernel (the lead operand as in launch_gemm_w4).
+  // 8871 tokens, top-2 of 8 experts, 4096 wide: gate-up with its SwiGLU (14336
+  // wide) 3700 -> 3150 us, down 1990 -> 1600, against the eight-wave form.
+  // The eight-wave form takes what its chains and 32-bit offsets do not: K of
+  // less than three slices, N of 2^22 and more.
+  if (K > 2 * CfgW4::BK && N < kW4MaxN) {
+    const int64_t tile_rows_max = (max_rows + CfgW4::BM - 1) / CfgW4::BM + E;
+    const int64_t items = tile_rows_max * ((N + CfgW4::BN - 1) / CfgW4::BN);
+    const GroupedGemm gg{gather, rows, tiles, E, (int)x_rows, w_stride, swiglu_f};
+    const auto go = [&](auto xl, auto rk) {
+      return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value, true>(
+          x, W, nullptr, y, max_rows, N, K, 1, K, nullptr, 0, 0, items, kChain, gg, s);
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    const bool ragged = K % CfgW4::BK != 0;
+    return K >= 8192 ? (ragged ? go(T{}, T{}) : go(T{}, F{})) : (ragged ? go(F{}, T{}) : go(F{}, F{}));
+  }
   return launch_grouped<CfgBig8>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f, s);
 }
 

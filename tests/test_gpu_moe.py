@@ -93,6 +93,21 @@ def test_fused_moe_sort_sizes(ops, T, E, k):
     assert_close(got, ref, "bf16", "fused_moe sort sizes")
 
 
+@pytest.mark.parametrize("fuse", [-1, 0])
+@pytest.mark.parametrize("T,H,F,E,k", [(1500, 264, 4096, 4, 2), (700, 192, 8200, 2, 2), (1200, 136, 1032, 9, 1)])
+def test_fused_moe_chained_tiles(ops, tune, fuse, T, H, F, E, k):
+    """Batches of more than 96 rows an expert run on the four-wave kernel, more
+    256x256 tiles than one round of the CUs as chains that cross from expert to
+    expert: a partial last K slice on either side, K of three slices, K past
+    8192 (x in the lead), rows of no expert, ragged tile-rows."""
+    tune(moe_fuse=fuse)
+    say(f"fused_moe chained tiles T={T} H={H} F={F} E={E} topk={k} fuse={fuse}")
+    ids = np.random.default_rng(T).integers(0, E, size=(T, k))
+    ids[::53, 0] = -1
+    got, ref = _moe_case(ops, T, H, F, E, k, seed=T + F, ids=ids)
+    assert_close(got, ref, "bf16", "fused_moe chained tiles")
+
+
 def test_fused_moe_one_hot_expert(ops):
     """Every token to expert 2 (600 rows: three 256-row tiles), the others empty."""
     say("fused_moe all tokens to one expert")
