@@ -365,77 +365,187 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_bf16_kernel(
 }
 
 // ------------------------------------------------------------ fp32 path ----
-// One wave per (token, query head).  Lane j scores key kv0 + j; probabilities
-// go through LDS and each lane accumulates D/64 output columns.
+// One workgroup of four waves per (prompt, query head, 32 queries); wave w
+// takes every fourth 32-key tile (w, w + 4, ...) with a running softmax of its
+// own, and the four partial results are merged in wave order through LDS.
+// Products on v_mfma_f32_32x32x2_f32, everything in fp32, exact expf.
+//
+// Scores are computed transposed (S^T = K Q^T), so a lane owns one query and
+// its accumulator element e is key 8 (e / 4) + 4 (lane / 32) + e % 4 of the
+// tile: exactly the B operand of MFMA e of O^T += V^T P^T when the A operand
+// takes V's row of that key, so no value changes lanes between the products.
+// K, Q and V are read straight into registers (16-byte chunks of K and Q
+// rows, 128-byte runs of V rows).  What bounds it is the chain of a tile (D
+// MFMAs of 64 cycles, its loads and the softmax) and, on short prompts, the
+// number of workgroups, hence the keys over the waves.  One prompt of 128, four
+// heads of 64: 7.9 us; one wave per (token, head) with a key per lane, each
+// lane walking its own K row, took 15.4.
 template <int D>
-__global__ __launch_bounds__(64) void attn_prefill_f32_kernel(
+__global__ __launch_bounds__(256) void attn_prefill_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     int64_t q_stride, int64_t kv_stride, float* __restrict__ o, const int32_t* __restrict__ cu,
-    int B, int Hq, int Hkv, float scale, int causal) {
-  constexpr int DPL = D / 64;
-  __shared__ float qs[D];
-  __shared__ float ps[64];
-  const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  // prompt of token t
-  int lo = 0, hi = B;  // cu[lo] <= t < cu[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (cu[mid] <= t) lo = mid; else hi = mid;
-  }
-  const int seq0 = cu[lo], L = cu[lo + 1] - seq0, i = t - seq0;
-  const int g = h / (Hq / Hkv);
-  for (int d = lane; d < D; d += 64) qs[d] = q[(int64_t)t * q_stride + (int64_t)h * D + d];
-  __syncthreads();
-  const int kv_end = causal ? i + 1 : L;
-  float m_run = -INFINITY, l_run = 0.f, acc[DPL] = {};
-  for (int kv0 = 0; kv0 < kv_end; kv0 += 64) {
-    const int j = kv0 + lane;
-    float s = -INFINITY;
-    if (j < kv_end) {
-      const float* kr = k + (int64_t)(seq0 + j) * kv_stride + (int64_t)g * D;
-      float dot = 0.f;
-      for (int d = 0; d < D; ++d) dot = fmaf(qs[d], kr[d], dot);
-      s = dot * scale;
-    }
-    const float m_new = fmaxf(m_run, wave_max(s));
-    const float p = j < kv_end ? expf(s - m_new) : 0.f;
-    const float alpha = expf(m_run - m_new);
-    l_run = l_run * alpha + wave_sum(p);
-    m_run = m_new;
-    ps[lane] = p;
-    __syncthreads();
-    const int n = min(64, kv_end - kv0);
+    int Hq, int Hkv, int levels, float scale, int causal) {
+  constexpr int DC = D / 8, DT = D / 32;  // chunk pairs of a row, 32-wide output tiles
+  constexpr int kCols = 64, kPad = kCols + 4;  // the merge takes 64 columns at a time
+  __shared__ __attribute__((aligned(16))) float os[4][32][kPad];
+  __shared__ float ms[4][32], ls[4][32];
+  const int lane = threadIdx.x & 63, fr = lane & 31, fh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bh = blockIdx.x / levels, level = blockIdx.x % levels;
+  const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hkv);
+  const int seq0 = cu[b], L = cu[b + 1] - seq0;
+  // (longest first, as many tiles as levels apart if the prompt has more)
+  for (int t = levels - 1 - level; t * 32 < L; t += levels) {
+    const int qi = t * 32 + fr;  // this lane's query
+    const float* qrow = q + (int64_t)(seq0 + min(qi, L - 1)) * q_stride + (int64_t)h * D;
+    f32x4 qf[DC];
 #pragma unroll
-    for (int c = 0; c < DPL; ++c) {
-      const int d = lane + c * 64;
-      float a = acc[c] * alpha;
-      for (int jj = 0; jj < n; ++jj)
-        a = fmaf(ps[jj], v[(int64_t)(seq0 + kv0 + jj) * kv_stride + (int64_t)g * D + d], a);
-      acc[c] = a;
-    }
-    __syncthreads();
-  }
+    for (int c = 0; c < DC; ++c) qf[c] = *reinterpret_cast<const f32x4*>(qrow + c * 8 + fh * 4);
+    const int kv_end = causal ? min(L, t * 32 + 32) : L;
+    const int ntile = (kv_end + 31) / 32;
+    f32x16 acc[DT] = {};
+    float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane half's keys
+    for (int kt = wave; kt < ntile; kt += 4) {
+      const int kv0 = kt * 32;
+      // (rows past the prompt: its last row again, masked below)
+      const float* krow = k + (int64_t)(seq0 + min(kv0 + fr, L - 1)) * kv_stride + (int64_t)g * D;
+      f32x4 kf[DC];
 #pragma unroll
-  for (int c = 0; c < DPL; ++c)
-    o[((int64_t)t * Hq + h) * D + lane + c * 64] = acc[c] / l_run;
+      for (int c = 0; c < DC; ++c) kf[c] = *reinterpret_cast<const f32x4*>(krow + c * 8 + fh * 4);
+      float vf[DT][16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int key = kv0 + 8 * (e >> 2) + 4 * fh + (e & 3);
+        const float* vrow = v + (int64_t)(seq0 + min(key, L - 1)) * kv_stride + (int64_t)g * D + fr;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) vf[dt][e] = vrow[dt * 32];
+      }
+      f32x16 st = {};
+#pragma unroll
+      for (int c = 0; c < DC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], qf[c][e], st, 0, 0, 0);
+      float tmax = -INFINITY;
+      const int last = causal ? min(qi, L - 1) : L - 1;  // last visible key
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int key = kv0 + 8 * (e >> 2) + 4 * fh + (e & 3);
+        st[e] = key <= last ? st[e] * scale : -INFINITY;
+        tmax = fmaxf(tmax, st[e]);
+      }
+      const float m_new = fmaxf(m_run, fmaxf(tmax, other_half(tmax)));
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m_run - m_use);
+      l_run *= alpha;
+      m_run = m_new;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int key = kv0 + 8 * (e >> 2) + 4 * fh + (e & 3);
+        st[e] = key <= last ? expf(st[e] - m_use) : 0.f;
+        l_run += st[e];
+      }
+      // A masked key contributes 0 x V, which is not 0 if V is an infinity or
+      // NaN: a tile with both is summed key by key.
+      bool plain = true;
+      if ((causal && kv0 + 31 > t * 32) || kv0 + 32 > L) {
+        float z = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) z = fmaf(vf[dt][e], 0.f, z);
+        plain = __builtin_amdgcn_ballot_w64(z != 0.f) == 0;  // (NaN != 0)
+      }
+      if (plain) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[dt][e], st[e], acc[dt], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          for (int hh = 0; hh < 2; ++hh) {
+            const int key = kv0 + 8 * (e >> 2) + 4 * hh + (e & 3);
+            const float p = __shfl(st[e], fr + 32 * hh, 64);
+            if (key > last) continue;
+            const float* vrow = v + (int64_t)(seq0 + key) * kv_stride + (int64_t)g * D + 4 * fh;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(p, vrow[dt * 32 + 8 * (r >> 2) + (r & 3)], acc[dt][r]);
+          }
+      }
+    }
+    l_run += other_half(l_run);
+    if (fh == 0) {
+      ms[wave][fr] = m_run;
+      ls[wave][fr] = l_run;
+    }
+#pragma unroll
+    for (int half = 0; half < D / kCols; ++half) {
+      if (half > 0) __syncthreads();  // the columns before are merged
+#pragma unroll
+      for (int dt = 0; dt < kCols / 32; ++dt)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const f32x16& a = acc[half * (kCols / 32) + dt];
+          *reinterpret_cast<f32x4*>(&os[wave][fr][dt * 32 + gq * 8 + fh * 4]) =
+              f32x4{a[4 * gq], a[4 * gq + 1], a[4 * gq + 2], a[4 * gq + 3]};
+        }
+      __syncthreads();
+      // eight threads a query, eight columns each
+      const int qr = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
+      if (t * 32 + qr < L) {
+        float m = ms[0][qr];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) m = fmaxf(m, ms[w][qr]);
+        const float m_use = m == -INFINITY ? 0.f : m;
+        float f[4], l = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          f[w] = ms[w][qr] == -INFINITY ? 0.f : expf(ms[w][qr] - m_use);
+          l = fmaf(f[w], ls[w][qr], l);
+        }
+        float* orow = o + ((int64_t)(seq0 + t * 32 + qr) * Hq + h) * D + half * kCols;
+#pragma unroll
+        for (int c = c0; c < kCols; c += 32) {
+          f32x4 a = *reinterpret_cast<const f32x4*>(&os[0][qr][c]) * f[0];
+#pragma unroll
+          for (int w = 1; w < 4; ++w) {
+            const f32x4 u = *reinterpret_cast<const f32x4*>(&os[w][qr][c]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(f[w], u[e], a[e]);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[e] /= l;
+          *reinterpret_cast<f32x4*>(orow + c) = a;
+        }
+      }
+    }
+    __syncthreads();  // the next tile reuses the LDS
+  }
 }
 
 static hipError_t launch_attn_prefill_f32(const void* q, const void* k, const void* v,
                                           int64_t q_stride, int64_t kv_stride, void* o,
-                                          const int32_t* cu, int32_t B, int64_t total_tokens,
+                                          const int32_t* cu, int32_t B, int64_t total_tokens, int32_t max_seqlen,
                                           int32_t Hq, int32_t Hkv, int32_t D, float scale, bool causal,
                                           hipStream_t s) {
-  const dim3 grid((unsigned)total_tokens, (unsigned)Hq);
-  if (D == 128)
-    hipLaunchKernelGGL((attn_prefill_f32_kernel<128>), grid, dim3(64), 0, s,
-                       static_cast<const float*>(q), static_cast<const float*>(k),
-                       static_cast<const float*>(v), q_stride, kv_stride, static_cast<float*>(o), cu,
-                       B, Hq, Hkv, scale, (int)causal);
-  else
-    hipLaunchKernelGGL((attn_prefill_f32_kernel<64>), grid, dim3(64), 0, s,
-                       static_cast<const float*>(q), static_cast<const float*>(k),
-                       static_cast<const float*>(v), q_stride, kv_stride, static_cast<float*>(o), cu,
-                       B, Hq, Hkv, scale, (int)causal);
+  // a workgroup per (prompt, head, 32-query tile up to max_seqlen); where that
+  // is more than a grid holds, each takes several tiles
+  const int64_t bh = (int64_t)B * Hq;
+  const int64_t longest = std::min<int64_t>(max_seqlen, total_tokens);
+  const int64_t levels = std::max<int64_t>(1, std::min<int64_t>((longest + 31) / 32, 0x7fffffff / bh));
+  const dim3 grid((unsigned)(bh * levels));
+#define OPS_PF32(DD)                                                                                              \
+  hipLaunchKernelGGL((attn_prefill_f32_kernel<DD>), grid, dim3(256), 0, s, static_cast<const float*>(q),          \
+                     static_cast<const float*>(k), static_cast<const float*>(v), q_stride, kv_stride,             \
+                     static_cast<float*>(o), cu, Hq, Hkv, (int)levels, scale, (int)causal)
+  if (D == 128) OPS_PF32(128);
+  else OPS_PF32(64);
+#undef OPS_PF32
   return hipGetLastError();
 }
 
@@ -444,8 +554,8 @@ hipError_t launch_attn_prefill(const void* q, const void* k, const void* v, int6
                                int64_t total_tokens, int32_t max_seqlen, int32_t Hq, int32_t Hkv,
                                int32_t D, float scale, bool causal, bool bf16, hipStream_t s) {
   if (!bf16)
-    return launch_attn_prefill_f32(q, k, v, q_stride, kv_stride, o, cu, B, total_tokens, Hq, Hkv, D,
-                                   scale, causal, s);
+    return launch_attn_prefill_f32(q, k, v, q_stride, kv_stride, o, cu, B, total_tokens, max_seqlen, Hq, Hkv, D, scale,
+                                   causal, s);
   const int G = Hq / Hkv;
   const int hpb = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
   const int BQ = 32 * (4 / hpb);

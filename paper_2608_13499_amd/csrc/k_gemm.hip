@@ -19,7 +19,7 @@
 // and the x tile the "B" operand, so each accumulator lane owns one output row
 // m and runs of 4 consecutive columns n, stored as 8-byte chunks.
 //
-// fp32 path: a plain LDS-tiled FMA kernel (exact fp32 products and sums).
+// (fp32: k_gemm_f32.hip.)
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -1040,53 +1040,6 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
   wait_vmem();  // no LDS DMA may still be in flight when the workgroup ends
 }
 
-// ------------------------------------------------------------ fp32 path ----
-// 64x64 output tile, 256 threads with 4x4 outputs each, K in slices of 16.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x,
-                                                       const float* __restrict__ W,
-                                                       const float* __restrict__ bias,
-                                                       float* __restrict__ y, int M, int N, int K) {
-  __shared__ float xs[16][64 + 4];
-  __shared__ float ws[16][64 + 4];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = threadIdx.x + i * 256;
-      const int r = idx >> 4, c = idx & 15;
-      const int k = k0 + c;
-      xs[c][r] = (m0 + r < M && k < K) ? x[(int64_t)(m0 + r) * K + k] : 0.f;
-      ws[c][r] = (n0 + r < N && k < K) ? W[(int64_t)(n0 + r) * K + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = xs[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = ws[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < N) y[(int64_t)m * N + n] = acc[i][j] + (bias ? bias[n] : 0.f);
-    }
-  }
-}
-
 // y[m][n] = bf16(sum over splits s of part[s][m][n] (in split order) + bias[n]),
 // four consecutive elements per thread (N is a multiple of 8).
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int splits,
@@ -1479,11 +1432,7 @@ hipError_t launch_linear(const LinearPlan& p, const void* x, const void* W, cons
       }
     default: break;
   }
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, static_cast<const float*>(x),
-                     static_cast<const float*>(W), static_cast<const float*>(bias),
-                     static_cast<float*>(y), (int)M, (int)N, (int)K);
-  return hipGetLastError();
+  return launch_linear_f32(x, W, bias, y, M, N, K, s);
 }
 
 }  // namespace opscale

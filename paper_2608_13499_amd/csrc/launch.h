@@ -50,6 +50,10 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
                                const int32_t* gather, const int32_t* rows, const int32_t* tiles, int32_t swiglu_f,
                                hipStream_t s);
 
+// The fp32 linear (k_gemm_f32.hip), K and N multiples of 4.
+hipError_t launch_linear_f32(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N, int64_t K,
+                             hipStream_t s);
+
 // The small-M (decode batch) bf16 linear: all M rows per workgroup, K split
 // over its waves.  Supported for 1 <= M <= kSkinnyMaxM with K % 32 == 0;
 // preferred over the tiled GEMM where it measured faster.

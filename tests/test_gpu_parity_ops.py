@@ -76,6 +76,26 @@ def test_linear(ops, dtype, M, N, K, bias):
     assert_close(f64(y.cpu()), oracle.linear(f64(x), f64(W), None if b is None else f64(b)), dtype, "linear")
 
 
+@pytest.mark.parametrize("M,N,K,bias", [(33, 36, 4, True), (1, 4, 28, False), (31, 100, 36, True), (65, 64, 132, False),
+                                        (64, 32, 260, True), (1500, 1532, 100, True), (1536, 2048, 64, False),
+                                        (1537, 2048, 132, False), (2000, 1540, 32, True)])
+def test_linear_f32_tiles(ops, M, N, K, bias):
+    """Both fp32 kernels: the 32x32 tile (K split over its waves in blocks of
+    32: fewer blocks than waves, partial blocks, ragged M and N), and from 192
+    tiles of 128x128 the large one (the last three shapes; 144 tiles before
+    them)."""
+    import torch
+    say(f"linear f32 tiles M={M} N={N} K={K} bias={bias}")
+    x = gen(31, "x", (M, K), "f32")
+    W = gen(31, "w_qkv", (N, K), "f32", std=0.02)
+    b = gen(31, "bias", (N,), "f32") if bias else None
+    args = (cuda(x), cuda(W), None if b is None else cuda(b))
+    y, y2 = ops.opscale_linear(*args), ops.opscale_linear(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    assert_close(f64(y.cpu()), oracle.linear(f64(x), f64(W), None if b is None else f64(b)), "f32", "linear f32")
+
+
 @pytest.mark.parametrize("tile", ["256x256", "192x256", "256x128", "256x256w8"])
 @pytest.mark.parametrize("M,N,K,bias", [(300, 264, 200, True), (513, 1024, 4096, False), (1, 256, 64, False),
                                         (700, 520, 136, False)])
@@ -332,6 +352,37 @@ def test_attn_prefill(ops, dtype, lens, Hq, Hkv, D, causal, packed):
     say(f"attn_prefill {dtype} lens={lens} Hq={Hq} Hkv={Hkv} D={D} causal={causal} packed={packed}")
     got, ref = _prefill_case(ops, dtype, lens, Hq, Hkv, D, causal, packed)
     assert_close(got, ref, dtype, "attn_prefill")
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,causal", [([31, 32, 33, 0, 129, 300, 1], 6, 2, 64, True),
+                                                  ([31, 0, 32, 33, 160, 257], 3, 1, 128, True),
+                                                  ([97, 65, 2], 4, 4, 128, False), ([300, 64], 2, 2, 64, False)])
+def test_attn_prefill_f32_tiles(ops, lens, Hq, Hkv, D, causal):
+    """The fp32 kernel's edges: prompts around one 32-query tile, fewer key
+    tiles than waves and more, a last tile of one key, both head widths."""
+    say(f"attn_prefill f32 tiles lens={lens} Hq={Hq} Hkv={Hkv} D={D} causal={causal}")
+    got, ref = _prefill_case(ops, "f32", lens, Hq, Hkv, D, causal, True)
+    assert_close(got, ref, "f32", "attn_prefill f32")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_attn_prefill_f32_future_is_not_read(ops, bad, D):
+    """An infinity or NaN in the keys and values of later tokens of the prompt,
+    or of the next prompt, leaves the queries before them unchanged."""
+    import torch
+    say(f"attn_prefill f32 future {bad} D={D}")
+    lens, H = [75, 40], 2
+    T = sum(lens)
+    q, k, v = (gen(33, t, (T, H, D), "f32") for t in ("q", "k", "v"))
+    ref = oracle.attn_prefill(f64(q), f64(k), f64(v), wl.cu_seqlens(lens), D ** -0.5, True)
+    k[70:75], v[70:75], k[80:], v[80:] = bad, bad, bad, bad
+    out = ops.opscale_attn_prefill(cuda(q), cuda(k), cuda(v), cuda(torch.from_numpy(wl.cu_seqlens(lens))), max(lens),
+                                   D ** -0.5)
+    torch.cuda.synchronize()
+    keep = np.r_[0:70, 75:80]
+    assert_close(f64(out.cpu())[keep], ref[keep], "f32", "queries before the bad keys")
+    assert not np.isfinite(f64(out.cpu())[np.r_[70:75, 80:T]]).any()
 
 
 @pytest.mark.parametrize("lens,Hq,Hkv,D", [
