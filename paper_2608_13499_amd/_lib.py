@@ -195,13 +195,21 @@ def _check(status: int):
 
 
 # ----------------------------------------------------------------- helpers --
+# A decode step of one sequence is a dozen launches of a few microseconds, so
+# what these functions cost is part of its time: no imports or stream objects
+# per call (the current stream's handle comes straight from torch).
+_DTYPES = None  # torch dtype -> opscale_dtype, filled on first use
+
+
 def _dt(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
-        return OPSCALE_BF16
-    if t.dtype == torch.float32:
-        return OPSCALE_F32
-    raise OpscaleError(OPSCALE_ERR_UNSUPPORTED, f"dtype {t.dtype} (supported: bfloat16, float32)")
+    global _DTYPES
+    if _DTYPES is None:
+        import torch
+        _DTYPES = {torch.bfloat16: OPSCALE_BF16, torch.float32: OPSCALE_F32}
+    dt = _DTYPES.get(t.dtype)
+    if dt is None:
+        raise OpscaleError(OPSCALE_ERR_UNSUPPORTED, f"dtype {t.dtype} (supported: bfloat16, float32)")
+    return dt
 
 
 def _dev(*tensors):
@@ -210,10 +218,17 @@ def _dev(*tensors):
             raise OpscaleError(OPSCALE_ERR_INVALID_ARG, "tensors must be on the GPU")
 
 
+_device, _raw_stream = None, None  # torch's current device and its current stream's handle
+
+
 def _stream(stream) -> int:
-    import torch
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        global _device, _raw_stream
+        if _raw_stream is None:
+            import torch
+            torch.cuda.current_stream()  # (initializes the device runtime)
+            _device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        return _raw_stream(_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -230,7 +245,7 @@ def _contig(name, t):
 
 # --------------------------------------------------------------- operators --
 def _heads_view(name, t_, H, D):
-    if t_.dim() != 3 or t_.shape[1] != H or t_.shape[2] != D or t_.stride(2) != 1 or t_.stride(1) != D:
+    if t_.dim() != 3 or tuple(t_.shape)[1:] != (H, D) or t_.stride()[1:] != (D, 1):
         raise OpscaleError(OPSCALE_ERR_INVALID_ARG, f"{name} must be [T, {H}, {D}] with contiguous heads")
 
 
@@ -240,18 +255,18 @@ def opscale_version() -> str:
 
 def opscale_rmsnorm(x, w, y=None, eps: float = 1e-5, stream=None, timed: bool = False):
     """y = x / sqrt(mean(x^2) + eps) * w over the last dim of x [M, H]."""
-    import torch
     lib = load()
     _dev(x, w, y)
     _contig("x", x)
     _contig("w", w)
     if y is None:
-        y = torch.empty_like(x)
-    _contig("y", y)
+        y = x.new_empty(x.shape)
+    else:
+        _contig("y", y)
     H = x.shape[-1]
     M = x.numel() // H if H else 0
     t = Timing() if timed else None
-    _check(lib.opscale_rmsnorm(_ptr(x), _ptr(w), _ptr(y), M, H, eps, _dt(x), _stream(stream),
+    _check(lib.opscale_rmsnorm(x.data_ptr(), w.data_ptr(), y.data_ptr(), M, H, eps, _dt(x), _stream(stream),
                                ctypes.byref(t) if t else None))
     return (y, t) if timed else y
 
@@ -268,7 +283,7 @@ def opscale_get_tuning(knob: int) -> int:
 def opscale_linear_workspace_size(M: int, N: int, K: int, dtype=None) -> int:
     import torch
     dt = OPSCALE_F32 if dtype == torch.float32 else OPSCALE_BF16
-    return int(load().opscale_linear_workspace_size(M, N, K, dt))
+    return load().opscale_linear_workspace_size(M, N, K, dt)
 
 
 def _linear_shapes(x, W):
@@ -294,33 +309,42 @@ def _linear_workspace(x, W, workspace):
 def opscale_linear(x, W, bias=None, y=None, workspace=None, stream=None, timed: bool = False):
     """y[M, N] = x[M, K] W[N, K]^T (+ bias).  `workspace` (a uint8 GPU tensor)
     is allocated by torch when None; False passes none."""
-    import torch
     lib = load()
     _dev(x, W, bias, y, workspace if workspace is not False else None)
-    for n, t_ in (("x", x), ("W", W), ("bias", bias), ("y", y)):
-        if t_ is not None:
-            _contig(n, t_)
+    _contig("x", x)
+    _contig("W", W)
+    if bias is not None:
+        _contig("bias", bias)
     M, N, K = _linear_shapes(x, W)
+    dt = _dt(x)
     if y is None:
-        y = torch.empty(*x.shape[:-1], N, dtype=x.dtype, device=x.device)
-    ws = _linear_workspace(x, W, workspace)
+        y = x.new_empty((*x.shape[:-1], N))
+    else:
+        _contig("y", y)
+    ws, nbytes = None, 0
+    if workspace is None:
+        nbytes = lib.opscale_linear_workspace_size(M, N, K, dt) if M else 0
+        if nbytes:
+            import torch
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+    elif workspace is not False:
+        ws, nbytes = workspace, workspace.numel() * workspace.element_size()
     t = Timing() if timed else None
-    _check(lib.opscale_linear(_ptr(x), _ptr(W), _ptr(bias), _ptr(y), M, N, K, _dt(x), _ptr(ws),
-                              0 if ws is None else ws.numel() * ws.element_size(), _stream(stream),
+    _check(lib.opscale_linear(x.data_ptr(), W.data_ptr(), None if bias is None else bias.data_ptr(), y.data_ptr(),
+                              M, N, K, dt, None if ws is None else ws.data_ptr(), nbytes, _stream(stream),
                               ctypes.byref(t) if t else None))
     return (y, t) if timed else y
 
 
 def opscale_swiglu(gate_up, out=None, stream=None, timed: bool = False):
     """out[M, F] = silu(gate_up[:, :F]) * gate_up[:, F:]."""
-    import torch
     lib = load()
     _dev(gate_up, out)
     _contig("gate_up", gate_up)
     F = gate_up.shape[-1] // 2
     M = gate_up.numel() // (2 * F)
     if out is None:
-        out = torch.empty(*gate_up.shape[:-1], F, dtype=gate_up.dtype, device=gate_up.device)
+        out = gate_up.new_empty((*gate_up.shape[:-1], F))
     _contig("out", out)
     t = Timing() if timed else None
     _check(lib.opscale_swiglu(_ptr(gate_up), _ptr(out), M, F, _dt(gate_up), _stream(stream),
@@ -338,7 +362,7 @@ def opscale_attn_prefill(q, k, v, cu_seqlens, max_seqlen: int, scale: float, cau
     _dev(q, k, v, cu_seqlens, out)
     T, Hq, D = q.shape
     Hkv = k.shape[1]
-    for name, t_, H in (("q", q, Hq), ("k", k, Hkv), ("v", v, Hkv)):
+    for name, t_ in (("q", q), ("k", k), ("v", v)):
         if t_.stride(2) != 1 or t_.stride(1) != D or t_.shape[0] != T:
             raise OpscaleError(OPSCALE_ERR_INVALID_ARG, f"{name} must be [T, H, D] with contiguous heads")
     if k.stride(0) != v.stride(0):
@@ -346,7 +370,7 @@ def opscale_attn_prefill(q, k, v, cu_seqlens, max_seqlen: int, scale: float, cau
     if cu_seqlens.dtype != torch.int32:
         raise OpscaleError(OPSCALE_ERR_INVALID_ARG, "cu_seqlens must be int32")
     if out is None:
-        out = torch.empty(T, Hq, D, dtype=q.dtype, device=q.device)
+        out = q.new_empty((T, Hq, D))
     _contig("out", out)
     B = cu_seqlens.numel() - 1
     t = Timing() if timed else None
@@ -375,11 +399,11 @@ def opscale_attn_decode(q, k_cache, v_cache, block_table, context_lens, max_cont
     B, Hq, D = q.shape
     _heads_view("q", q, Hq, D)
     num_blocks, bs, Hkv, _ = k_cache.shape
-    need = opscale_attn_decode_workspace_size(B, Hq, D, max_context_len)
     if workspace is None:
+        need = lib.opscale_attn_decode_workspace_size(B, Hq, D, max_context_len)
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
     if out is None:
-        out = torch.empty(B, Hq, D, dtype=q.dtype, device=q.device)
+        out = q.new_empty((B, Hq, D))
     _contig("out", out)
     t = Timing() if timed else None
     _check(lib.opscale_attn_decode(_ptr(q), q.stride(0), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
@@ -460,13 +484,13 @@ def opscale_reshape_and_cache(k, v, k_cache, v_cache, slot_mapping, stream=None,
 
 def opscale_add_rmsnorm(x, residual, w, y=None, eps: float = 1e-5, stream=None, timed: bool = False):
     """residual <- x + residual; y = rmsnorm(residual) * w.  Returns y."""
-    import torch
     lib = load()
     _dev(x, residual, w, y)
-    for n, t_ in (("x", x), ("residual", residual), ("w", w)):
-        _contig(n, t_)
+    _contig("x", x)
+    _contig("residual", residual)
+    _contig("w", w)
     if y is None:
-        y = torch.empty_like(x)
+        y = x.new_empty(x.shape)
     _contig("y", y)
     H = x.shape[-1]
     M = x.numel() // H if H else 0
@@ -518,8 +542,8 @@ def opscale_fused_moe(x, w1, w2, topk_ids, topk_weights, out=None, workspace=Non
     E, F2, _ = w1.shape
     topk = topk_ids.shape[1]
     out = torch.empty_like(x) if out is None else out
-    need = opscale_fused_moe_workspace_size(T, H, F2 // 2, E, topk)
     if workspace is None:
+        need = opscale_fused_moe_workspace_size(T, H, F2 // 2, E, topk)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x.device)
     t = Timing() if timed else None
     _check(load().opscale_fused_moe(_ptr(x), _ptr(w1), _ptr(w2), _ptr(topk_ids), _ptr(topk_weights), _ptr(out), T,
