@@ -124,6 +124,22 @@ __device__ __forceinline__ float wave_sum_f(float v) {
   return (lane(0) + lane(16)) + (lane(32) + lane(48));
 }
 
+// A row's sum over its WPR waves (1, or the 4 of the workgroup), given each
+// lane's part; every lane of the row gets it.  Fixed order.
+template <int WPR>
+__device__ __forceinline__ float row_sum(float v) {
+  v = wave_sum_f(v);
+  if constexpr (WPR > 1) {
+    __shared__ float part[WPR];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = part[0];
+#pragma unroll
+    for (int w = 1; w < WPR; ++w) v += part[w];
+  }
+  return v;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Wait for every outstanding vector-memory operation of this wave (including

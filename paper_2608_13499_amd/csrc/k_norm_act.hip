@@ -8,16 +8,18 @@
 namespace opscale {
 
 // ------------------------------------------------------------- RMS Norm ----
-// One wave per row.  VPL = 16-byte vectors per lane held in registers (a row of
-// up to VPL*64*16 bytes is read once); VPL == 0 selects the streaming variant
-// for longer rows, which reads the row a second time (from L2) to normalize.
-template <bool BF16, int VPL>
+// WPR waves per row: the workgroup's four, or one for short rows.  VPL = 16-byte
+// vectors per lane held in registers (a row of up to VPL*WPR*64*16 bytes is
+// read once); VPL == 0 selects the streaming variant for longer rows, which
+// reads the row a second time (from L2) to normalize.
+template <bool BF16, int VPL, int WPR>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* x, const void* __restrict__ w,
                                                       void* y, int64_t M,
                                                       int H, float eps) {
   constexpr int EPV = BF16 ? 8 : 4;  // elements per 16-byte vector
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int STEP = 64 * WPR;
+  const int lane = threadIdx.x & (STEP - 1);  // lane of the row
+  const int64_t row = (int64_t)blockIdx.x * (4 / WPR) + threadIdx.x / STEP;
   if (row >= M) return;
   const int nvec = H / EPV;
   const u32x4* xr = reinterpret_cast<const u32x4*>(static_cast<const char*>(x) + row * (int64_t)H * (BF16 ? 2 : 4));
@@ -65,54 +67,57 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* x, const void*
     u32x4 v[VPL], g[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
-      const int idx = lane + i * 64;
+      const int idx = lane + i * STEP;
       v[i] = idx < nvec ? xr[idx] : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
-      const int idx = lane + i * 64;
+      const int idx = lane + i * STEP;
       g[i] = idx < nvec ? wr[idx] : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int i = 0; i < VPL; ++i) ss += sq(v[i]);
-    ss = wave_sum_f(ss);
+    ss = row_sum<WPR>(ss);
     const float r = rsqrtf(ss / (float)H + eps);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
-      const int idx = lane + i * 64;
+      const int idx = lane + i * STEP;
       if (idx < nvec) yr[idx] = scale(v[i], g[i], r);
     }
   } else {
-    for (int idx = lane; idx < nvec; idx += 64) ss += sq(xr[idx]);
-    ss = wave_sum(ss);
+    for (int idx = lane; idx < nvec; idx += STEP) ss += sq(xr[idx]);
+    ss = row_sum<WPR>(ss);
     const float r = rsqrtf(ss / (float)H + eps);
-    for (int idx = lane; idx < nvec; idx += 64) yr[idx] = scale(xr[idx], wr[idx], r);
+    for (int idx = lane; idx < nvec; idx += STEP) yr[idx] = scale(xr[idx], wr[idx], r);
   }
 }
 
-template <bool BF16>
+template <bool BF16, int WPR>
 static hipError_t rmsnorm_dispatch(const void* x, const void* w, void* y, int64_t M, int64_t H,
                                    float eps, hipStream_t s) {
-  const int epv = BF16 ? 8 : 4;
-  const int64_t nvec = H / epv;
-  const int vpl = (int)((nvec + 63) / 64);
-  const dim3 grid((unsigned)((M + 3) / 4)), block(256);
+  constexpr int kRows = 4 / WPR;  // rows of a workgroup
+  const int64_t nvec = H / (BF16 ? 8 : 4);
+  const int vpl = (int)((nvec + 64 * WPR - 1) / (64 * WPR));
+  const dim3 grid((unsigned)((M + kRows - 1) / kRows)), block(256);
   const int h = (int)H;
-#define OPS_RMS(V) hipLaunchKernelGGL((rmsnorm_kernel<BF16, V>), grid, block, 0, s, x, w, y, M, h, eps)
+#define OPS_RMS(V) hipLaunchKernelGGL((rmsnorm_kernel<BF16, V, WPR>), grid, block, 0, s, x, w, y, M, h, eps)
   if (vpl <= 1) OPS_RMS(1);
   else if (vpl <= 2) OPS_RMS(2);
-  else if (vpl <= 4) OPS_RMS(4);
-  else if (vpl <= 8) OPS_RMS(8);
-  else if (vpl <= 16) OPS_RMS(16);
-  else OPS_RMS(0);
+  else if constexpr (WPR > 1) {
+    if (vpl <= 4) OPS_RMS(4);
+    else if (vpl <= 8) OPS_RMS(8);
+    else if (vpl <= 16) OPS_RMS(16);
+    else OPS_RMS(0);
+  }
 #undef OPS_RMS
   return hipGetLastError();
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int64_t H, float eps,
                           bool bf16, hipStream_t s) {
-  return bf16 ? rmsnorm_dispatch<true>(x, w, y, M, H, eps, s)
-              : rmsnorm_dispatch<false>(x, w, y, M, H, eps, s);
+  if (H / (bf16 ? 8 : 4) > kWaveRowMaxVec)
+    return bf16 ? rmsnorm_dispatch<true, 4>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 4>(x, w, y, M, H, eps, s);
+  return bf16 ? rmsnorm_dispatch<true, 1>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 1>(x, w, y, M, H, eps, s);
 }
 
 // --------------------------------------------------------------- SwiGLU ----

@@ -14,6 +14,14 @@ namespace opscale {
 // -1 means automatic (the shape decides).
 int32_t tuning(opscale_tune knob);
 
+// RMS Norm and residual norm: rows of more than this many 16-byte vectors take
+// a workgroup each, shorter ones a wave (a workgroup would have idle lanes).
+// A whole row in one wave is one chain of loads, reduction and stores, and few
+// rows leave most of the chip idle.  Measured (us, H = 4096, wave / workgroup
+// per row, residual norm): 3.0 / 2.0 for one row, 3.5 / 2.3 for 48, 8.2 / 7.1
+// for 1023, 50.7 / 45.8 for 8871; RMS Norm 2.5 / 1.9, 2.9 / 2.2, 4.9 / 4.6,
+// 24.8 / 23.3.
+constexpr int64_t kWaveRowMaxVec = 128;
 hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int64_t H, float eps,
                           bool bf16, hipStream_t s);
 

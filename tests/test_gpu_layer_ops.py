@@ -109,6 +109,33 @@ def test_add_rmsnorm(ops, dtype, M, H, inplace):
     assert_close(f64(y.cpu()), ry, dtype, "add_rmsnorm y")
 
 
+@pytest.mark.parametrize("dtype,H", [("bf16", 1024), ("bf16", 1032), ("bf16", 2056), ("bf16", 4104), ("bf16", 8192),
+                                     ("f32", 512), ("f32", 516), ("f32", 4092)])
+def test_norm_row_lengths(ops, dtype, H):
+    """Both norms at the row lengths where they change: the longest row of one
+    wave (128 vectors of 16 bytes) and the shortest of a workgroup, rows that
+    end inside a round of the workgroup's lanes, the longest residual row; the
+    RMS Norm also past its register rows."""
+    import torch
+    say(f"norms {dtype} H={H}")
+    M = 5
+    x, r = gen(35, "x", (M, H), dtype), gen(35, "attn_out", (M, H), dtype)
+    w = gen(35, "w_norm", (H,), dtype, std=0.02, mean=1.0)
+    rd = cuda(r)
+    y = ops.opscale_add_rmsnorm(cuda(x), rd, cuda(w), eps=1e-5)
+    z = ops.opscale_rmsnorm(cuda(x), cuda(w), eps=1e-5)
+    torch.cuda.synchronize()
+    ry, rr = oracle.add_rmsnorm(f64(x), f64(r), f64(w), 1e-5)
+    assert_close(f64(rd.cpu()), rr, dtype, "residual")
+    assert_close(f64(y.cpu()), ry, dtype, "add_rmsnorm")
+    assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, "rmsnorm")
+    for long in (8 * H + 8, 32 * H + 8):
+        x, w = gen(36, "x", (2, long), dtype), gen(36, "w_norm", (long,), dtype, std=0.02, mean=1.0)
+        z = ops.opscale_rmsnorm(cuda(x), cuda(w), eps=1e-5)
+        torch.cuda.synchronize()
+        assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, f"rmsnorm H={long}")
+
+
 # ----------------------------------------------------------- a whole layer ---
 def _layer_weights(seed, shape, dtype):
     H, Hq, Hkv, D, F = shape.hidden, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.ffn
