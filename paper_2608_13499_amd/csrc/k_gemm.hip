@@ -1041,14 +1041,26 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
 }
 
 // y[m][n] = bf16(sum over splits s of part[s][m][n] (in split order) + bias[n]),
-// four consecutive elements per thread (N is a multiple of 8).
+// four consecutive elements per thread (N is a multiple of 8).  BATCH ranges'
+// partials are requested together: eight for outputs of at most a workgroup per
+// CU, which wait on latency (48 x 4096 over 8 ranges: 0.7 us less), one at a
+// time for larger ones, which have other waves to run (256 x 4096: 0.6 less).
+template <int BATCH>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int splits,
                                                             const __bf16* __restrict__ bias,
                                                             __bf16* __restrict__ y, int64_t MN, int N) {
   const int64_t n4 = MN / 4;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
     f32x4 a = reinterpret_cast<const f32x4*>(part)[i];
-    for (int sp = 1; sp < splits; ++sp) a += reinterpret_cast<const f32x4*>(part + (int64_t)sp * MN)[i];
+    for (int s0 = 1; s0 < splits; s0 += BATCH) {
+      f32x4 v[BATCH];
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j)
+        if (s0 + j < splits) v[j] = reinterpret_cast<const f32x4*>(part + (int64_t)(s0 + j) * MN)[i];
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j)
+        if (s0 + j < splits) a += v[j];
+    }
     if (bias) {
       const int n = (int)((i * 4) % N);
       const u32x2 bb = *reinterpret_cast<const u32x2*>(bias + n);
@@ -1225,8 +1237,9 @@ hipError_t launch_splitk_reduce(const float* part, int splits, const void* bias,
                                 hipStream_t s) {
   const int64_t MN = M * N;
   const unsigned blocks = (unsigned)std::min<int64_t>(4096, (MN / 4 + 255) / 256);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, s, part, splits,
-                     static_cast<const __bf16*>(bias), static_cast<__bf16*>(y), MN, (int)N);
+  const auto kern = blocks <= (unsigned)kNumCUs ? &splitk_reduce_kernel<8> : &splitk_reduce_kernel<1>;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, part, splits, static_cast<const __bf16*>(bias),
+                     static_cast<__bf16*>(y), MN, (int)N);
   return hipGetLastError();
 }
 
@@ -1316,30 +1329,37 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
   const int32_t force_tile = tuning(OPSCALE_TUNE_GEMM_TILE);
   const int32_t skinny = tuning(OPSCALE_TUNE_GEMM_SKINNY);
   p.path = LinearPlan::kTiled;
-  // Decode-sized M: the weights dominate and large tiles would leave most CUs
-  // idle.  The small-M kernel reduces its K split in LDS and needs no
-  // workspace.
-  if (force_tile < 0 && skinny != 0 &&
-      (skinny == 1 ? skinny_linear_supported(M, N, K) : skinny_linear_preferred(M, N, K))) {
-    p.path = LinearPlan::kSkinny;
-    return p;
-  }
-  // Decode batches of 33-128 rows with K up to 8192: the weight-streaming
-  // kernel, its K split (if any) through the workspace.  Measured cold on
-  // the 8B-layer projections it is 3-13 % faster there than the split-K tiles
-  // (QKV, O, gate-up at M = 64 and 128); at 192-256 rows and for the
-  // 14336-wide down projection the tiles below are faster.
+  // Decode batches of up to 128 rows: the weight-streaming kernel, its K split
+  // (if any) through the workspace; or the small-M kernel, which reduces its
+  // K split in LDS and needs no workspace, but reads all of x per 16 columns.
+  // That extra x traffic (M N K / 8 bytes from L2) against the other's second
+  // launch and partials, which grow with its K ranges, draws the line.
+  // Measured (us, streaming / small-M kernel; splits in brackets): QKV 6144 x
+  // 4096 [4] M = 4 14.7 / 14.4, M = 8 14.7 / 15.7; O 4096 x 4096 [8] M = 8 13.3 /
+  // 9.6, M = 16 13.5 / 11.4, M = 32 13.9 / 15.2; down 4096 x 14336 [8] M = 4 27.6 /
+  // 24.7, M = 8 27.4 / 27.4; gate-up 28672 x 4096 [1] M = 1 41.6 / 39.9, M = 4
+  // 40.1 / 44.2, M = 16 40.4 / 64.5; 57344 x 8192 [1] M = 2 163 / 153, M = 4 equal.
+  // Beyond 32 rows with K past 8192 the split-K tiles are as fast or faster (8192
+  // x 28672 at M = 48 89.7 against 91.5); past 128 rows everywhere.
   const int32_t dec = tuning(OPSCALE_TUNE_GEMM_DECODE);
-  if (force_tile < 0 && dec != 0 && decode_linear_supported(M, N, K) &&
-      (dec == 1 || (M > 32 && M <= 128 && K <= 8192))) {
+  LinearPlan d{};
+  if (force_tile < 0 && dec != 0 && decode_linear_supported(M, N, K) && (dec == 1 || K <= 8192 || M <= 32)) {
     const int ds = tuning(OPSCALE_TUNE_GEMM_SPLITK) == 0 ? 1 : decode_linear_splits(M, N, K);
     if (ds <= 1 || split_ok) {
-      p.path = LinearPlan::kDecode;
-      p.splits = ds;
-      p.ws_bytes = ds > 1 ? decode_linear_ws_bytes(M, N, K) : 0;
+      d.path = LinearPlan::kDecode;
+      d.splits = ds;
+      d.ws_bytes = ds > 1 ? decode_linear_ws_bytes(M, N, K) : 0;
+    }
+  }
+  const bool streamed = d.path == LinearPlan::kDecode;
+  if (force_tile < 0 && skinny != 0 && !(streamed && dec == 1)) {
+    const bool few = streamed ? M <= 2 || (double)M * N * K <= 3.5e7 * d.splits : skinny_linear_preferred(M, N, K);
+    if (skinny_linear_supported(M, N, K) && (skinny == 1 || few)) {
+      p.path = LinearPlan::kSkinny;
       return p;
     }
   }
+  if (streamed) return d;
   // Otherwise decode-sized M splits K over workgroups (fp32 partials in the
   // workspace, summed in split order by a second kernel).  Tile rows follow
   // M: 64 up to 64 rows (the matrix cores work on little padding), 128 up to

@@ -119,10 +119,12 @@ bool skinny_linear_supported(int64_t M, int64_t N, int64_t K) {
   return M >= 1 && M <= kSkinnyMaxM && K % 32 == 0 && N >= 1;
 }
 
-// Measured on MI355X over the 8B-layer shapes at M = 1 ... 512 (cold caches):
-// this path wins at M <= 16 for every shape, and at M <= 32 wherever the
-// tiled GEMM has few 256x256 tiles (QKV, O, down: 16-24); beyond that the
-// split-K tiled GEMM wins (and with many tiles, gate-up's 112, the plain one).
+// Where the weight-streaming kernel does not take the shape (K not a multiple
+// of 64, or no workspace for its K split).  Measured over the 8B-layer shapes
+// at M = 1 ... 512 (cold caches) against the tiles: this path wins at M <= 16
+// for every shape, and at M <= 32 wherever the tiled GEMM has few 256x256 tiles
+// (QKV, O, down: 16-24); beyond that the split-K tiled GEMM wins (and with many
+// tiles, gate-up's 112, the plain one).
 bool skinny_linear_preferred(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
   return skinny_linear_supported(M, N, K) && (M <= 16 || (M <= 32 && tiles < 64));

@@ -71,12 +71,12 @@ bool skinny_linear_preferred(int64_t M, int64_t N, int64_t K);
 hipError_t launch_linear_skinny(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
                                 int64_t K, hipStream_t s);
 
-// The decode-batch bf16 linear (k_gemm_decode.hip): 128 output columns and
-// all M rows per workgroup, the weights streamed into registers, K split
+// The decode-batch bf16 linear (k_gemm_decode.hip): 80 to 128 output columns
+// and all M rows per workgroup, the weights streamed into registers, K split
 // over workgroups up to about one per CU (fp32 partials [splits, M, N] in the
 // workspace, then launch_splitk_reduce).  Supported for 1 <= M <=
 // kDecodeMaxM with K % 64 == 0.
-constexpr int64_t kDecodeMaxM = 256;
+constexpr int64_t kDecodeMaxM = 128;
 bool decode_linear_supported(int64_t M, int64_t N, int64_t K);
 int decode_linear_splits(int64_t M, int64_t N, int64_t K);
 size_t decode_linear_ws_bytes(int64_t M, int64_t N, int64_t K);

@@ -203,6 +203,32 @@ def test_linear_decode_batch(ops, tune, M, N, K, bias):
     assert_close(f64(y0.cpu()), ref, "bf16", "linear without a workspace")
 
 
+@pytest.mark.parametrize("M,N,K,bias", [
+    (16, 10232, 1024, True), (17, 24584, 128, False), (32, 24576, 512, True), (33, 4096, 4096, False),
+    (64, 6136, 1536, True), (65, 28672, 192, True), (128, 200, 4672, False), (100, 8, 1152, True), (2, 28664, 64, False),
+])
+def test_linear_decode_batch_shapes(ops, tune, M, N, K, bias):
+    """The weight-streaming kernel at its edges: the most and fewest rows of
+    each row-block count (16, 32, 64, 128), five to eight waves of 16 columns
+    with a ragged last workgroup, one to nine K ranges of one to 64 slices
+    (each workgroup starting at another one), fewer slices than the ring
+    holds and a partial last round of it."""
+    import torch
+    tune(gemm_decode=1)
+    say(f"linear bf16 decode-batch shapes M={M} N={N} K={K} bias={bias}")
+    x = gen(30, "x", (M, K), "bf16")
+    W = gen(30, "w_qkv", (N, K), "bf16", std=0.02)
+    b = gen(30, "bias", (N,), "bf16") if bias else None
+    args = (cuda(x), cuda(W), None if b is None else cuda(b))
+    need = ops.opscale_linear_workspace_size(M, N, K)
+    ws = torch.full((max(need, 16),), 0x7f, dtype=torch.uint8, device="cuda")
+    y, y2 = ops.opscale_linear(*args, workspace=ws), ops.opscale_linear(*args, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    ref = oracle.linear(f64(x), f64(W), None if b is None else f64(b))
+    assert_close(f64(y.cpu()), ref, "bf16", "linear")
+
+
 @pytest.mark.parametrize("M,N,K,bias", [(777, 1304, 2120, True), (2048, 6144, 4096, False), (256, 512, 64, True),
                                         (1300, 1000, 2056, True), (520, 384, 8256, False)])
 def test_linear_four_and_eight_waves_agree(ops, tune, M, N, K, bias):
