@@ -514,6 +514,18 @@ def test_attn_decode(ops, dtype, ctx, Hq, Hkv, D, bs):
     assert_close(got, ref, dtype, "attn_decode")
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("ctx", [[1], [33, 0], [512, 32 * 16 + 1], [32 * 63, 40], [32 * 65 + 5, 31, 1],
+                                 [9000, 0, 70, 5, 17, 300, 64, 33]])
+def test_attn_decode_many_segments(ops, ctx, D):
+    """Few sequences over many workgroups: the merge by four waves of 16
+    segments, at one segment, one wave's 16 and one more, 63 to 66 (a second
+    block of 64), and with most of a batch's segments in one sequence."""
+    say(f"attn_decode many segments ctx={ctx} D={D}")
+    got, ref = _decode_case(ops, "bf16", ctx, 8, 2, D, 16)
+    assert_close(got, ref, "bf16", "attn_decode many segments")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_attn_decode_invalid_block_is_skipped(ops, dtype):
     say(f"attn_decode invalid block id {dtype}")
