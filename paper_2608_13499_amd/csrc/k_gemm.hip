@@ -8,11 +8,12 @@
 // use four waves of 128x128 sub-tiles, one per SIMD, with the accumulators in
 // AGPRs (gemm_bf16_w4_kernel), the grouped mixture-of-experts GEMMs among them;
 // the eight-wave form of the same tile (two waves of 128x64 per SIMD) takes
-// what that kernel's chains and 32-bit offsets do not.  Problems
-// whose last round of 256x256 tiles would be mostly idle take 192x256 or
-// 256x128 tiles; decode-sized M splits K.  Rows
-// and K columns beyond the matrix read as zeros through the buffer
-// descriptor's range check, so ragged M, N and K need no separate code path.
+// what that kernel's chains and 32-bit offsets do not.  Sizes that give few such
+// tiles take 128x256 ones (gemm_bf16_h4_kernel) where that is faster, and
+// decode-sized M splits K.  (192x256 and 256x128 tiles, CfgT192 and CfgMid, run
+// only where the tile knob asks for them.)  Rows and K columns beyond the matrix
+// read as zeros through the buffer descriptor's range check, so ragged M, N and
+// K need no separate code path.
 //
 // Both operands are K-contiguous, which is what an MFMA operand lane wants: a
 // lane holds 8 consecutive k of one row.  The W tile is the MFMA "A" operand
@@ -1040,6 +1041,254 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
   wait_vmem();  // no LDS DMA may still be in flight when the workgroup ends
 }
 
+// A 128x256 tile as four waves of 128x64 (each all the tile's rows and 64 of its
+// columns), for the sizes where 256x256 tiles are too few: decode batches past
+// 128 rows and chunks of a few hundred.  Loads, fragments and bookkeeping are
+// the four-wave 256x256 kernel's; the LDS (160 KB) holds rings of four x slices
+// and three W slices, so up to 112 KB are in flight per CU.  What bounds it is
+// the LDS (a slice moves 96 KB of fragments and 48 KB of loads per 1024 cycles
+// of MFMAs) and, below 256 rows, the weight stream.  Unsplit launches start
+// each column tile at another slice of K and wrap around: in step, all tiles
+// would read the same few HBM channels (128 x 28672 x 4096: 68.7 -> 55.1 us); K
+// ranges already differ.
+// us, the 256x256, 128x256 and 256x128 tiles used before -> this one: 256 x 6144 x
+// 4096 32.0 -> 28.1, 256 x 28672 x 4096 87 -> 63, 256 x 4096 x 14336 50.5 -> 45.3, 256
+// x 10240 x 8192 70.5 -> 55.4, 512 x 4096 x 4096 41.3 -> 31.2, 1023 x 4096 x 4096 49.7 ->
+// 43.8.
+template <bool RAGGED_K>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_h4_kernel(const __bf16* __restrict__ x,
+                                                              const __bf16* __restrict__ W,
+                                                              const __bf16* __restrict__ bias,
+                                                              __bf16* __restrict__ y, int M, int N, int K_total,
+                                                              int group_m, int kchunk,
+                                                              float* __restrict__ part) {
+  using C = CfgW4;  // (row and chunk geometry of an LDS row)
+  constexpr int BM = 128, BN = 256, BK = 64, WM = 128, WN = 64;
+  constexpr int MI = 16, TM = WM / MI, TN = WN / MI, KS = 2;  // 8 x 4 MFMA tiles per wave
+  constexpr int kWaves = 4, LX = 4, LW = 8;                    // loads per wave of an x / W slice
+  constexpr int XS = 4, WS = 3;                                // ring depths
+  constexpr int XB = BM * 128, WB = BN * 128;
+  constexpr uint32_t kOutOfRange = 0xfffffff0u;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+
+  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
+  const int ld = K_total;
+  const int split = blockIdx.x / tiles;
+  int tm, tn;
+  tile_coords(xcd_remap(blockIdx.x - split * tiles, (uint32_t)tiles), tiles_m, tiles_n, group_m, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN, m_rows = min(BM, M - m0);
+  const int k_begin = split * kchunk, K = min(K_total - k_begin, kchunk);
+  const int nk = (K + BK - 1) / BK;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wn = wave;
+
+  const int rl = lane / 8, pc = lane % 8;
+  const int xc = pc ^ rl, wc = pc ^ ((rl & 3) | ((wave & 1) << 2));
+  uint32_t xro[LX], wro[LW];
+#pragma unroll
+  for (int g = 0; g < LX; ++g) xro[g] = (uint32_t)(((g * kWaves + wave) * 8 + rl) * ld * 2) + (uint32_t)(xc << 4);
+#pragma unroll
+  for (int g = 0; g < LW; ++g) wro[g] = (uint32_t)(((g * kWaves + wave) * 8 + rl) * ld * 2) + (uint32_t)(wc << 4);
+
+  f32x4 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{};
+
+  // the slice this tile starts at
+  const int rot = kchunk < K_total ? 0 : tiles_n <= 65536 ? (int)((uint32_t)(tn * nk) / (uint32_t)tiles_n) : tn % nk;
+  // Load cursors of x and W: base, records (none once every slice is loaded:
+  // the rest read zeros into buffers no wave reads any more), slices left,
+  // slices until the wrap to the range's first, k left in the range.
+  struct Cursor {
+    uint64_t first, base;
+    uint32_t rec;
+    int left, wrap, k;
+  };
+  auto cursor = [&](const __bf16* p, int rows) {
+    const uint64_t first = (uint64_t)(uintptr_t)(p + k_begin);
+    return Cursor{first, first + (uint32_t)rot * (BK * 2), (uint32_t)(((int64_t)(rows - 1) * ld + K) * 2), nk, nk - rot,
+                  K - rot * BK};
+  };
+  Cursor cx = cursor(x + (int64_t)m0 * ld, m_rows), cw = cursor(W + (int64_t)n0 * ld, min(BN, N - n0));
+  // one slice further, in two parts that each fit between two MFMAs
+  auto advance = [&](Cursor& c, int step) {
+    if (step == 0) {
+      pin_s(c.base);
+      c.base += BK * 2;
+      --c.wrap;
+      --c.left;
+      if (RAGGED_K) c.k -= BK;
+      pin_s(c.base);
+      pin_s(c.wrap);
+      pin_s(c.left);
+    } else {
+      pin_s(c.wrap);
+      c.base = c.wrap > 0 ? c.base : c.first;
+      if (RAGGED_K) c.k = c.wrap > 0 ? c.k : K;
+      c.wrap = c.wrap > 0 ? c.wrap : 0x40000000;
+      c.rec = c.left > 0 ? c.rec : 0;
+      pin_s(c.base);
+      pin_s(c.wrap);
+      pin_s(c.rec);
+    }
+  };
+  auto load = [&](const Cursor& c, uint32_t voff, int chunk, uint32_t dst, int g) {
+    if (RAGGED_K) voff = chunk * 8 < c.k ? voff : kOutOfRange;
+    buffer_load16_lds<kNoL1>(make_rsrc((const void*)(uintptr_t)c.base, c.rec),
+                             (OPS_LDS char*)(uintptr_t)(dst + (g * kWaves + wave) * 1024), voff);
+  };
+  auto load_x = [&](uint32_t dst, int g) { load(cx, xro[g], xc, dst, g); };
+  auto load_w = [&](uint32_t dst, int g) { load(cw, wro[g], wc, dst, g); };
+
+  const int fr = lane & 15, fh = lane >> 4;
+  uint32_t x_off[KS], w_off[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const int ch = ((4 * ks + fh) ^ (fr & 7)) << 4;
+    x_off[ks] = fr * 128 + ch;
+    w_off[ks] = (wn * WN + (fr >> 2) * 8 + (fr & 3)) * 128 + ch;
+  }
+  bf16x8 a[2][TN], b[2][TM];
+  uint32_t ax, aw;
+  auto read_frag = [&](int buf, int r) {
+    auto xf = [&](int j) { return lds_frag<C>((const OPS_LDS char*)(uintptr_t)(ax + j * MI * 128)); };
+    auto wf = [&](int i) { return lds_frag<C>((const OPS_LDS char*)(uintptr_t)(aw + ((i >> 1) * 32 + (i & 1) * 4) * 128)); };
+    if (r == 0) b[buf][0] = xf(0);
+    else if (r == 1) a[buf][0] = wf(0);
+    else if (r < TM + 1) b[buf][r - 1] = xf(r - 1);
+    else a[buf][r - TM] = wf(r - TM);
+  };
+  auto kstep = [&](auto buf_c, auto side) {
+    constexpr int buf = decltype(buf_c)::value;
+#pragma unroll
+    for (int q = 0; q < TN * TM; ++q) {
+      mfma_agpr(acc[q / TM][q % TM], a[buf][q / TM], b[buf][q % TM]);
+      if (q % 2 == 0 && q / 2 < TN + TM) read_frag(buf ^ 1, q / 2);
+      side(q);
+    }
+  };
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(OPS_LDS char*)smem_raw;
+  // x buffers of slices s .. s + 3, W buffers of slices s .. s + 2
+  uint32_t x0 = lds0, x1 = lds0 + XB, x2 = lds0 + 2 * XB, x3 = lds0 + 3 * XB;
+  uint32_t w0 = lds0 + XS * XB, w1 = w0 + WB, w2 = w0 + 2 * WB;
+  // X(0), W(0), X(1), W(1), X(2), W(2), the order the loop goes on in
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+#pragma unroll
+    for (int g = 0; g < LX; ++g) load_x(s == 0 ? x0 : s == 1 ? x1 : x2, g);
+    advance(cx, 0);
+    advance(cx, 1);
+#pragma unroll
+    for (int g = 0; g < LW; ++g) load_w(s == 0 ? w0 : s == 1 ? w1 : w2, g);
+    advance(cw, 0);
+    advance(cw, 1);
+  }
+  wait_vmcnt<2 * (LX + LW)>();
+  barrier_keep_loads();
+  ax = x_off[0] + x0;
+  aw = w_off[0] + w0;
+#pragma unroll
+  for (int r = 0; r < TN + TM; ++r) read_frag(0, r);
+  ax = x_off[1] + x0;
+  aw = w_off[1] + w0;
+  asm volatile("s_nop 1" ::);
+  int left = nk;
+  do {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    // k-step 0 of slice s: loads X(s + 3) into x3
+    kstep(B0{}, [&](int q) {
+      if ((q & 7) == 3) load_x(x3, q >> 3);
+      if (q == 28) advance(cx, 0);
+      if (q == 29) advance(cx, 1);
+      if (q == 30) {
+        ax = x_off[0] + x1;
+        pin_v(ax);
+      }
+      if (q == 31) {
+        aw = w_off[0] + w1;
+        pin_v(aw);
+      }
+    });
+    // slice s + 1 has landed: newer are X(s + 2), W(s + 2), X(s + 3)
+    wait_vmcnt<2 * LX + LW>();
+    barrier_keep_loads();
+    // k-step 1: W(s + 3) into w0 (slice s is read)
+    kstep(B1{}, [&](int q) {
+      if ((q & 3) == 1) load_w(w0, q >> 2);
+      if (q == 26) {
+        const uint32_t t = x0;
+        x0 = x1;
+        x1 = x2;
+        x2 = x3;
+        x3 = t;
+        pin_s(x0);
+        pin_s(x1);
+        pin_s(x2);
+        pin_s(x3);
+      }
+      if (q == 28) {
+        ax = x_off[1] + x0;
+        pin_v(ax);
+      }
+      if (q == 29) {
+        aw = w_off[1] + w1;
+        pin_v(aw);
+        --left;
+        pin_s(left);
+      }
+      if (q == 30) advance(cw, 0);
+      if (q == 31) {
+        advance(cw, 1);
+        const uint32_t t = w0;
+        w0 = w1;
+        w1 = w2;
+        w2 = t;
+        pin_s(w0);
+        pin_s(w1);
+        pin_s(w2);
+      }
+    });
+  } while (left > 0);
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::);
+  const int c0 = wn * WN + fh * 8;
+  if (part) {
+    float* pb = part + ((int64_t)split * M + m0) * N + n0;
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      const int r = j * MI + fr;
+#pragma unroll
+      for (int i = 0; i < TN; ++i) {
+        const int c = c0 + (i >> 1) * 32 + (i & 1) * 4;
+        const f32x4 v = agpr_read(acc[i][j]);
+        if (r < m_rows && c < N - n0) *reinterpret_cast<f32x4*>(pb + (int64_t)r * N + c) = v;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      const int r = j * MI + fr;
+#pragma unroll
+      for (int p = 0; p < TN / 2; ++p) {
+        f32x4 lo = agpr_read(acc[2 * p][j]), hi = agpr_read(acc[2 * p + 1][j]);
+        const int n = n0 + c0 + p * 32;
+        if (r >= m_rows || n >= N) continue;
+        if (bias) {
+          const u32x4 bb = *reinterpret_cast<const u32x4*>(bias + n);
+          lo += f32x4{bf_lo(bb[0]), bf_hi(bb[0]), bf_lo(bb[1]), bf_hi(bb[1])};
+          hi += f32x4{bf_lo(bb[2]), bf_hi(bb[2]), bf_lo(bb[3]), bf_hi(bb[3])};
+        }
+        *reinterpret_cast<u32x4*>(y + (int64_t)(m0 + r) * N + n) =
+            u32x4{pack_bf2(lo[0], lo[1]), pack_bf2(lo[2], lo[3]), pack_bf2(hi[0], hi[1]), pack_bf2(hi[2], hi[3])};
+      }
+    }
+  }
+  wait_vmem();
+}
+
 // y[m][n] = bf16(sum over splits s of part[s][m][n] (in split order) + bias[n]),
 // four consecutive elements per thread (N is a multiple of 8).  BATCH ranges'
 // partials are requested together: eight for outputs of at most a workgroup per
@@ -1233,6 +1482,33 @@ static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias,
   return hipGetLastError();
 }
 
+// The 128x256 tile: tiles, or splits K ranges of each.
+constexpr int kH4Rows = 128, kH4Cols = 256;
+static hipError_t launch_gemm_h4(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
+                                 int64_t K, hipStream_t s, int splits, float* part) {
+  constexpr int kLds = (4 * kH4Rows + 3 * kH4Cols) * 128;  // rings of four x and three W slices
+  static const hipError_t attr = [] {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_h4_kernel<false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    return e != hipSuccess ? e
+                           : hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_h4_kernel<true>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  }();
+  if (attr != hipSuccess) return attr;
+  const int64_t tiles_m = (M + kH4Rows - 1) / kH4Rows, tiles_n = (N + kH4Cols - 1) / kH4Cols;
+  const int64_t kchunk = splits > 1 ? split_chunk(K, splits, 64) : K;
+  const int nsplit = splits > 1 ? split_ranges(K, splits, 64) : 1;
+  const int group_m = (int)std::min<int64_t>(tiles_m, std::max<int64_t>(2 * kMinGroupRows, kGroupBytes / (kH4Rows * K * 2)));
+  const auto kern = K % 64 ? &gemm_bf16_h4_kernel<true> : &gemm_bf16_h4_kernel<false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * nsplit)), dim3(256), kLds, s,
+                     static_cast<const __bf16*>(x), static_cast<const __bf16*>(W), static_cast<const __bf16*>(bias),
+                     static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m, (int)kchunk,
+                     nsplit > 1 ? part : nullptr);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || nsplit <= 1) return e;
+  return launch_splitk_reduce(part, nsplit, bias, y, M, N, s);
+}
+
 hipError_t launch_splitk_reduce(const float* part, int splits, const void* bias, void* y, int64_t M, int64_t N,
                                 hipStream_t s) {
   const int64_t MN = M * N;
@@ -1243,14 +1519,13 @@ hipError_t launch_splitk_reduce(const float* part, int splits, const void* bias,
   return hipGetLastError();
 }
 
-// Split-K for small M: when at most half as many 256x128 tiles as CUs exist,
-// K is cut into floor(kNumCUs / tiles) ranges (each at least 512 wide), so
-// about kNumCUs workgroups run.  (A split that only lifts 129-255 tiles a
-// little past the CU count measured slower than no split.)  0: no split.
-template <class C>
-static int splitk_count(int64_t M, int64_t N, int64_t K) {
+// Split-K for small M: when at most half as many bm x bn tiles as CUs exist, K
+// is cut into floor(kNumCUs / tiles) ranges (each at least 512 wide), so about
+// kNumCUs workgroups run.  (A split that only lifts 129-255 tiles a little past
+// the CU count measured slower than no split.)  0: no split.
+static int splitk_count(int bm, int bn, int64_t M, int64_t N, int64_t K) {
   if (M > kSplitKMaxM || K < 1024) return 0;
-  const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
+  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int64_t s = std::min<int64_t>(kNumCUs / tiles, K / 512);
   return s >= 2 ? (int)s : 0;
 }
@@ -1317,17 +1592,15 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
 }
 
 // The tiled configurations a plan can name.
-enum TileCfg { kCfgBig8 = 0, kCfgT192 = 1, kCfgMid = 2, kCfgSk64 = 3, kCfgSk128 = 4, kCfgW4 = 5 };
+enum TileCfg { kCfgBig8 = 0, kCfgT192 = 1, kCfgMid = 2, kCfgSk64 = 3, kCfgSk128 = 4, kCfgW4 = 5, kCfgH4 = 6 };
 
-template <class C>
+// workspace of a K split (64-wide slices), and of a split tail of bm x bn tiles
 static size_t split_bytes(int64_t M, int64_t N, int64_t K, int splits) {
-  return (size_t)split_ranges(K, splits, C::BK) * M * N * sizeof(float);
+  return (size_t)split_ranges(K, splits, 64) * M * N * sizeof(float);
 }
-
-template <class C>
-static size_t tail_bytes(int64_t M, int64_t N, int64_t K, int tail_splits) {
-  const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
-  return (size_t)split_ranges(K, tail_splits, C::BK) * (tiles % kNumCUs) * C::BM * C::BN * sizeof(float);
+static size_t tail_bytes(int bm, int bn, int64_t M, int64_t N, int64_t K, int tail_splits) {
+  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  return (size_t)split_ranges(K, tail_splits, 64) * (tiles % kNumCUs) * bm * bn * sizeof(float);
 }
 
 // One rule for the path of a linear, shared by the workspace query and the
@@ -1370,38 +1643,17 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
     }
   }
   if (streamed) return d;
-  // Otherwise decode-sized M splits K over workgroups (fp32 partials in the
-  // workspace, summed in split order by a second kernel).  Tile rows follow
-  // M: 64 up to 64 rows (the matrix cores work on little padding), 128 up to
-  // 256; larger M takes 256 rows with 256 or 128 columns, whichever gives
-  // more workgroups (ties: 256, which re-reads x half as often).
-  if (force_tile < 0 && split_ok && tuning(OPSCALE_TUNE_GEMM_SPLITK) != 0) {
-    if (M <= 64) {
-      p.splits = splitk_count<CfgSk64>(M, N, K);
-      p.cfg = kCfgSk64;
-      if (p.splits > 1) { p.ws_bytes = split_bytes<CfgSk64>(M, N, K, p.splits); return p; }
-    } else if (M <= 256) {
-      p.splits = splitk_count<CfgSk128>(M, N, K);
-      p.cfg = kCfgSk128;
-      if (p.splits > 1) { p.ws_bytes = split_bytes<CfgSk128>(M, N, K, p.splits); return p; }
-    } else {
-      const int s_wide = splitk_count<CfgBig8>(M, N, K), s_mid = splitk_count<CfgMid>(M, N, K);
-      const int64_t w_wide = (int64_t)s_wide * ((N + 255) / 256), w_mid = (int64_t)s_mid * ((N + 127) / 128);
-      if (w_wide >= w_mid && s_wide > 1) {
-        p.cfg = N < kW4MaxN ? kCfgW4 : kCfgBig8; p.splits = s_wide; p.ws_bytes = split_bytes<CfgW4>(M, N, K, s_wide); return p;
-      }
-      if (s_mid > 1) { p.cfg = kCfgMid; p.splits = s_mid; p.ws_bytes = split_bytes<CfgMid>(M, N, K, s_mid); return p; }
+  // Otherwise up to 128 rows split K over workgroups (fp32 partials in the
+  // workspace, summed in split order by a second kernel) on tiles of 64 or 128
+  // rows, so that the matrix cores work on little padding.
+  if (force_tile < 0 && split_ok && tuning(OPSCALE_TUNE_GEMM_SPLITK) != 0 && M <= 128) {
+    p.splits = M <= 64 ? splitk_count(64, 256, M, N, K) : splitk_count(128, 256, M, N, K);
+    p.cfg = M <= 64 ? kCfgSk64 : kCfgSk128;
+    if (p.splits > 1) {
+      p.ws_bytes = split_bytes(M, N, K, p.splits);
+      return p;
     }
     p.splits = 0;
-  }
-  // 129-256 rows whose 128-row tiles already fill more than half the GPU
-  // (the gate-up projection of a 256-sequence decode batch: 224 tiles) run
-  // unsplit as 128-row tiles: their 3-stage ring keeps two weight slices per
-  // CU in flight.
-  if (force_tile < 0 && M > 128 && M <= 256 && K >= 1024 &&
-      2 * ((N + CfgSk128::BN - 1) / CfgSk128::BN) > kNumCUs / 2) {
-    p.cfg = kCfgSk128;
-    return p;
   }
   // A last round at most half full runs split over K: 2-4 ranges per tile
   // (at most one workgroup per CU in all), each at least 8 slices long.
@@ -1412,34 +1664,58 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
     const int ts = (int)std::min<int64_t>(std::min<int64_t>(4, kNumCUs / tail), K / (8 * 64));
     return ts < 2 ? 0 : ts;
   };
-  // One workgroup per CU at a time, so a launch runs in full rounds plus a
-  // last one (a split last round counts as 1 / splits of a round).  Pick the
-  // tile whose rounds x tile area x relative per-element cost is smallest:
-  // 256x256 moves the fewest operand bytes per flop; 192x256 (measured about
-  // 17 % more time per element) and 256x128 (about 60 % more) fill the last
-  // round better when 256x256 would leave it mostly idle.
-  struct Choice { int bm, bn; double cost; };
-  static constexpr Choice choices[] = {{256, 256, 1.0}, {192, 256, 1.17}, {256, 128, 1.6}};
-  int best = 0;
-  if (force_tile >= 0 && force_tile <= 3) {
-    best = force_tile == 3 ? 0 : force_tile;
-  } else {
-    double best_t = 0;
-    for (int c = 0; c < 3; ++c) {
-      const int64_t tiles = ((M + choices[c].bm - 1) / choices[c].bm) * ((N + choices[c].bn - 1) / choices[c].bn);
-      const int ts = tail_splits(tiles);
-      const double rounds = (double)(tiles / kNumCUs) + (tiles % kNumCUs == 0 ? 0.0 : ts ? 1.0 / ts : 1.0);
-      const double t = rounds * choices[c].bm * choices[c].bn * choices[c].cost;
-      if (c == 0 || t < best_t) { best = c; best_t = t; }
+  auto tiles_of = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (force_tile >= 0) {
+    static constexpr struct { int bm, bn, cfg; } forced[] = {
+        {256, 256, kCfgW4}, {192, 256, kCfgT192}, {256, 128, kCfgMid}, {256, 256, kCfgBig8}};
+    const auto& f = forced[force_tile];
+    p.cfg = f.cfg == kCfgW4 && N >= kW4MaxN ? kCfgBig8 : f.cfg;
+    p.tail_splits = tail_splits(tiles_of(f.bm, f.bn));
+    if (p.tail_splits > 1) p.ws_bytes = tail_bytes(f.bm, f.bn, M, N, K, p.tail_splits);
+    return p;
+  }
+  // 256x256 or 128x256 tiles, whole or split over K (small M), whichever the
+  // estimate below has faster.  One workgroup runs per CU; a launch takes full
+  // rounds and a last one, a slice of K takes longer the more CUs run (power
+  // and bandwidth shared), and a K split pays for its partials (written and
+  // read) and a second launch.  Microseconds per slice fitted to measured
+  // launches: 256x256 1.1 up to half the CUs, 1.34 on all (1500 x 6144 x 4096
+  // 144 tiles 75 us, 3000 x 4096 x 4096 192 tiles 83, 4500 x 28672 x 4096 full
+  // rounds); 128x256 0.70 to 0.86 (700 x 6144 144 tiles 50, 1500 x 4096 192 tiles
+  // 53, 512 x 28672 full rounds).  (192x256 and 256x128 tiles of the older
+  // kernels, 1.3 and 1.9 times the time per element, never win.)
+  struct Tile { int bm, cfg; double busy, all, fixed; };
+  static constexpr Tile kTiles[] = {{256, kCfgW4, 1.1, 1.34, 5.0}, {128, kCfgH4, 0.70, 0.86, 4.0}};
+  double best = 0;
+  for (const Tile& t : kTiles) {
+    const int64_t tiles = tiles_of(t.bm, 256), slices = (K + 63) / 64;
+    auto slice_us = [&](int64_t wgs) {
+      const double u = (double)wgs / kNumCUs;
+      return t.busy + std::max(0.0, u - 0.5) * 2 * (t.all - t.busy);
+    };
+    auto consider = [&](double us, int splits, int tail, size_t bytes) {
+      if (best != 0 && us >= best) return;
+      best = us;
+      p.cfg = t.cfg == kCfgW4 && N >= kW4MaxN ? kCfgBig8 : t.cfg;
+      p.splits = splits;
+      p.tail_splits = tail;
+      p.ws_bytes = bytes;
+    };
+    auto partials_us = [](double bytes) { return 3.0 + 2 * bytes / 7e6; };
+    const int64_t full = tiles / kNumCUs, rem = tiles % kNumCUs;
+    const int ts = t.cfg == kCfgW4 ? tail_splits(tiles) : 0;
+    const size_t tail_b = ts > 1 ? tail_bytes(t.bm, 256, M, N, K, ts) : 0;
+    double us = full * (slices * t.all) + t.fixed * (t.cfg == kCfgW4 ? 1 : full + (rem ? 1 : 0));
+    if (rem) us += ts > 1 ? (double)slices / ts * t.all + partials_us((double)tail_b) : slices * slice_us(rem);
+    consider(us, 0, ts, tail_b);
+    const int sp = split_ok && tuning(OPSCALE_TUNE_GEMM_SPLITK) != 0 ? splitk_count(t.bm, 256, M, N, K) : 0;
+    if (sp > 1) {
+      const int ranges = split_ranges(K, sp, 64);
+      const size_t b = split_bytes(M, N, K, sp);
+      consider((double)(split_chunk(K, sp, 64) / 64) * slice_us(tiles * ranges) + t.fixed + partials_us((double)b), sp, 0,
+               b);
     }
   }
-  p.cfg = best == 0 ? (force_tile == 3 || N >= kW4MaxN ? kCfgBig8 : kCfgW4) : best == 1 ? kCfgT192 : kCfgMid;
-  p.tail_splits = tail_splits(((M + choices[best].bm - 1) / choices[best].bm) *
-                              ((N + choices[best].bn - 1) / choices[best].bn));
-  if (p.tail_splits > 1)
-    p.ws_bytes = p.cfg == kCfgBig8 || p.cfg == kCfgW4 ? tail_bytes<CfgBig8>(M, N, K, p.tail_splits)
-                 : p.cfg == kCfgT192 ? tail_bytes<CfgT192>(M, N, K, p.tail_splits)
-                                     : tail_bytes<CfgMid>(M, N, K, p.tail_splits);
   return p;
 }
 
@@ -1454,6 +1730,7 @@ hipError_t launch_linear(const LinearPlan& p, const void* x, const void* W, cons
     case LinearPlan::kTiled:
       switch (p.cfg) {
         case kCfgBig8: return launch_gemm_bf16<CfgBig8>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
+        case kCfgH4: return launch_gemm_h4(x, W, bias, y, M, N, K, s, p.splits, part);
         case kCfgW4: return launch_gemm_w4(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
         case kCfgT192: return launch_gemm_bf16<CfgT192>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);
         case kCfgMid: return launch_gemm_bf16<CfgMid>(x, W, bias, y, M, N, K, s, p.splits, p.tail_splits, part);

@@ -229,6 +229,31 @@ def test_linear_decode_batch_shapes(ops, tune, M, N, K, bias):
     assert_close(f64(y.cpu()), ref, "bf16", "linear")
 
 
+@pytest.mark.parametrize("M,N,K,bias", [
+    (129, 264, 64, True), (130, 8, 200, False), (256, 520, 128, True), (385, 1032, 192, False), (257, 2056, 1000, True),
+    (140, 5000, 1096, False), (256, 4096, 2048, True), (300, 776, 3080, True), (512, 4104, 4096, False),
+])
+def test_linear_128_row_tiles(ops, tune, M, N, K, bias):
+    """Past 128 rows and few 256x256 tiles: the 128x256 tile, whole (each
+    column tile starting at another slice of K, one to 16 slices, the last a
+    part of one) and split over K (ranges of 8 slices and more, the last one
+    ragged), ragged M and N, through a poisoned workspace and without one."""
+    import torch
+    say(f"linear bf16 128-row tiles M={M} N={N} K={K} bias={bias}")
+    x = gen(32, "x", (M, K), "bf16")
+    W = gen(32, "w_qkv", (N, K), "bf16", std=0.02)
+    b = gen(32, "bias", (N,), "bf16") if bias else None
+    args = (cuda(x), cuda(W), None if b is None else cuda(b))
+    ws = torch.full((max(ops.opscale_linear_workspace_size(M, N, K), 16),), 0x7f, dtype=torch.uint8, device="cuda")
+    y, y2 = ops.opscale_linear(*args, workspace=ws), ops.opscale_linear(*args, workspace=ws)
+    y0 = ops.opscale_linear(*args, workspace=False)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    ref = oracle.linear(f64(x), f64(W), None if b is None else f64(b))
+    assert_close(f64(y.cpu()), ref, "bf16", "linear 128-row tiles")
+    assert_close(f64(y0.cpu()), ref, "bf16", "linear 128-row tiles without a workspace")
+
+
 @pytest.mark.parametrize("M,N,K,bias", [(777, 1304, 2120, True), (2048, 6144, 4096, False), (256, 512, 64, True),
                                         (1300, 1000, 2056, True), (520, 384, 8256, False)])
 def test_linear_four_and_eight_waves_agree(ops, tune, M, N, K, bias):
