@@ -1549,9 +1549,13 @@ static hipError_t launch_grouped(const void* x, int64_t x_rows, const void* W, i
 }
 
 int32_t grouped_gemm_tile_rows(int64_t rows, int32_t E) {
-  // about 96 rows or fewer per expert (decode batches): 64-row tiles, so the
-  // matrix cores do not spend most of a 256-row tile on padding
-  return rows <= (int64_t)96 * E ? CfgRow64::BM : CfgBig8::BM;
+  // about 64 rows or fewer per expert (decode batches): 64-row tiles, so the
+  // matrix cores do not spend most of a 256-row tile on padding; beyond, the
+  // four-wave kernel's tiles, which read each expert's weights once where
+  // 64-row ones read them twice (us, 64 / 256 rows, 64 experts of 2560, top-8: 56
+  // rows an expert 689 / 724, 75 rows 840 / 743, 96 rows 884 / 763; 8 experts of
+  // 14336, top-2: 75 rows 699 / 708, 150 rows 1049 / 714)
+  return rows <= (int64_t)64 * E ? CfgRow64::BM : CfgBig8::BM;
 }
 
 hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int64_t w_stride, void* y,

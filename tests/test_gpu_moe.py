@@ -96,7 +96,7 @@ def test_fused_moe_sort_sizes(ops, T, E, k):
 @pytest.mark.parametrize("fuse", [-1, 0])
 @pytest.mark.parametrize("T,H,F,E,k", [(1500, 264, 4096, 4, 2), (700, 192, 8200, 2, 2), (1200, 136, 1032, 9, 1)])
 def test_fused_moe_chained_tiles(ops, tune, fuse, T, H, F, E, k):
-    """Batches of more than 96 rows an expert run on the four-wave kernel, more
+    """Batches of more than 64 rows an expert run on the four-wave kernel, more
     256x256 tiles than one round of the CUs as chains that cross from expert to
     expert: a partial last K slice on either side, K of three slices, K past
     8192 (x in the lead), rows of no expert, ragged tile-rows."""
