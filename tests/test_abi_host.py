@@ -330,3 +330,36 @@ def test_moe_validation(lib):
     assert t(A16, A16 * 2, A16 * 3, 10, 64, 17, 1, None, None) == 1  # topk > 16
     assert t(A16, A16 * 2, A16 * 3, 10, 2000, 2, 1, None, None) == 1
     assert t(None, None, None, 0, 8, 2, 1, None, None) == 0
+
+
+def test_linear_workspace_over_sizes(lib):
+    """The plan of a linear over sizes that reach every path (small-M,
+    weight-streaming, 64/128/256-row tiles whole and split, split tails, ragged
+    K, N past the 32-bit tiles): the scratch it asks for is whole fp32 partials
+    of at most one 256x256 tile per CU, none where the K splits are turned off,
+    and the same when asked again."""
+    import random
+    rng = random.Random(7)
+    SPLITK, TAIL, BF16 = 2, 3, 1
+    sizes = [(1, 8, 64), (2, 57344, 8192), (8, 1 << 22, 64), (300, (1 << 22) + 8, 192), (8871, 28672, 4096)]
+    for _ in range(3000):
+        m = int(2 ** rng.uniform(0, 15))
+        n = 8 * max(1, int(2 ** rng.uniform(0, 13)))
+        k = rng.choice([8, 32, 64]) * max(1, int(2 ** rng.uniform(0, 8)))
+        sizes.append((m, n, k))
+    size = lib.opscale_linear_workspace_size
+    some = 0
+    try:
+        for m, n, k in sizes:
+            b = size(m, n, k, BF16)
+            some += b > 0
+            assert b % 4 == 0 and b <= 256 * 256 * 256 * 4, (m, n, k, b)
+            assert size(m, n, k, BF16) == b
+            assert size(m, n, k, 0) == 0  # fp32 needs none
+        assert some > 100
+        lib.opscale_set_tuning(SPLITK, 0)
+        lib.opscale_set_tuning(TAIL, 0)
+        assert all(size(m, n, k, BF16) == 0 for m, n, k in sizes)
+    finally:
+        lib.opscale_set_tuning(SPLITK, -1)
+        lib.opscale_set_tuning(TAIL, -1)
