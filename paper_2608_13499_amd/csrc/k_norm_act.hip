@@ -122,8 +122,9 @@ hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int6
 
 // --------------------------------------------------------------- SwiGLU ----
 // grid.x covers one row's 16-byte output vectors (256 threads x VPT vectors
-// each), grid.y strides over rows.
-template <bool BF16, int VPT>
+// each), grid.y strides over rows.  STREAM: nontemporal accesses, for batches
+// that do not stay in the caches between the projections around this anyway.
+template <bool BF16, int VPT, bool STREAM>
 __global__ __launch_bounds__(256) void swiglu_kernel(const void* __restrict__ gu, void* __restrict__ out,
                                                      int64_t M, int64_t F) {
   constexpr int EPV = BF16 ? 8 : 4;
@@ -139,8 +140,8 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const void* __restrict__ gu
     for (int i = 0; i < VPT; ++i) {
       const int64_t idx = base + i * 256;
       if (idx < nvec) {
-        gv[i] = __builtin_nontemporal_load(g + idx);
-        uv[i] = __builtin_nontemporal_load(u + idx);
+        gv[i] = STREAM ? __builtin_nontemporal_load(g + idx) : g[idx];
+        uv[i] = STREAM ? __builtin_nontemporal_load(u + idx) : u[idx];
       }
     }
 #pragma unroll
@@ -160,21 +161,31 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const void* __restrict__ gu
           r[e] = __float_as_uint(g0 / (1.f + expf(-g0)) * __uint_as_float(ua[e]));
         }
       }
-      __builtin_nontemporal_store(r, o + idx);
+      if (STREAM) __builtin_nontemporal_store(r, o + idx);
+      else o[idx] = r;
     }
   }
 }
 
-hipError_t launch_swiglu(const void* gu, void* out, int64_t M, int64_t F, bool bf16, hipStream_t s) {
-  constexpr int VPT = 2;
-  const int64_t nvec = F / (bf16 ? 8 : 4);
+template <bool BF16, int VPT, bool STREAM>
+static hipError_t swiglu_dispatch(const void* gu, void* out, int64_t M, int64_t F, hipStream_t s) {
+  const int64_t nvec = F / (BF16 ? 8 : 4);
   const unsigned gx = (unsigned)((nvec + 256 * VPT - 1) / (256 * VPT));
   const unsigned gy = (unsigned)(M < 65535 ? M : 65535);
-  if (bf16)
-    hipLaunchKernelGGL((swiglu_kernel<true, VPT>), dim3(gx, gy), dim3(256), 0, s, gu, out, M, F);
-  else
-    hipLaunchKernelGGL((swiglu_kernel<false, VPT>), dim3(gx, gy), dim3(256), 0, s, gu, out, M, F);
+  hipLaunchKernelGGL((swiglu_kernel<BF16, VPT, STREAM>), dim3(gx, gy), dim3(256), 0, s, gu, out, M, F);
   return hipGetLastError();
+}
+
+hipError_t launch_swiglu(const void* gu, void* out, int64_t M, int64_t F, bool bf16, hipStream_t s) {
+  // Up to 16 million outputs of wide rows (of narrow ones, up to 256 rows):
+  // cached accesses and one vector a thread, i.e. twice the workgroups.  us, two
+  // nontemporal / one cached: F = 14336, M = 1 2.1 / 1.8, 256 9.5 / 7.9, 512 11.8 /
+  // 9.0, 1023 16.5 / 14.5, 2048 28.9 / 35.9, 8871 123 / 134; F = 2560, M = 256 3.55 /
+  // 3.33, 512 4.8 / 5.2, 1023 7.1 / 8.0.
+  const bool small = M * F <= ((int64_t)1 << 24) && (F >= 8192 || M <= 256);
+  if (small)
+    return bf16 ? swiglu_dispatch<true, 1, false>(gu, out, M, F, s) : swiglu_dispatch<false, 1, false>(gu, out, M, F, s);
+  return bf16 ? swiglu_dispatch<true, 2, true>(gu, out, M, F, s) : swiglu_dispatch<false, 2, true>(gu, out, M, F, s);
 }
 
 // ---------------------------------------------------------------- flush ----

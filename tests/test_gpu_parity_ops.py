@@ -360,6 +360,19 @@ def test_swiglu(ops, dtype, M, F):
     assert_close(f64(out.cpu()), oracle.swiglu(f64(u)), dtype, "swiglu")
 
 
+@pytest.mark.parametrize("dtype,M,F", [("bf16", 256, 40), ("bf16", 257, 40), ("bf16", 257, 8184), ("bf16", 2, 8192),
+                                       ("bf16", 2048, 8192), ("bf16", 2049, 8192), ("f32", 5, 8196)])
+def test_swiglu_small_and_streaming(ops, dtype, M, F):
+    """Both forms (cached, one vector a thread; nontemporal, two) at the line
+    between them: 256 rows of narrow outputs, 2^24 outputs of wide ones."""
+    import torch
+    say(f"swiglu forms {dtype} M={M} F={F}")
+    u = gen(37, "gate_up", (M, 2 * F), dtype, std=3.0)
+    out = ops.opscale_swiglu(cuda(u))
+    torch.cuda.synchronize()
+    assert_close(f64(out.cpu()), oracle.swiglu(f64(u)), dtype, "swiglu")
+
+
 # -------------------------------------------------------- prefill attention --
 def _prefill_case(ops, dtype, lens, Hq, Hkv, D, causal, packed, seed=41):
     import torch
