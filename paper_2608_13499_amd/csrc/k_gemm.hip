@@ -1462,7 +1462,7 @@ static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias,
   // The ring gives half a slice more of lead to one operand: the one with
   // fewer distinct blocks among the 32 tiles an XCD runs at once (x when a
   // group spans at most 4 tile-rows, i.e. K >= 8192; W for the 8-row groups of
-  // K = 4096).  Same-box, flushed, measured on the ring's first form: the 8B
+  // K = 4096).  On one card, flushed, measured on the ring's first form: the 8B
   // gate-up 1579 -> 1526 us with W leading, down 769 -> 752 us and the 70B
   // gate-up and down 3-4 % faster with x leading.
   const bool xlead = group_m <= 4, ragged = K % C::BK != 0;
