@@ -66,6 +66,27 @@ def test_rope(ops, dtype, T, Hq, Hkv, D, theta, maxpos):
     assert torch.equal(got[0], qkv[0]), "position 0 must be the identity"
 
 
+# A thread requests three quads of pairs at once: head counts at and past the
+# edges of what the workgroup's 768 cover (16 or 8 quads a head).
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [("bf16", 1, 1, 64), ("bf16", 40, 8, 128), ("bf16", 48, 1, 128),
+                                            ("bf16", 96, 8, 128), ("f32", 96, 1, 64), ("f32", 64, 64, 128)])
+def test_rope_head_counts(ops, dtype, Hq, Hkv, D):
+    import torch
+    say(f"rope head counts {dtype} Hq={Hq} Hkv={Hkv} D={D}")
+    T = 5
+    qkv = _packed(33, T, Hq, Hkv, D, dtype)
+    pos = np.array([0, 1, 77, 8191, 131071], np.int32)
+    qd = cuda(qkv)
+    q, k, _ = _views(qd, Hq, Hkv, D)
+    ops.opscale_rope(q, k, cuda(torch.from_numpy(pos)), 500000.0)
+    torch.cuda.synchronize()
+    gq, gk, gv = _views(qd.cpu(), Hq, Hkv, D)
+    qh, kh, vh = _views(qkv, Hq, Hkv, D)
+    assert_close(f64(gq), oracle.rope(f64(qh), pos, 500000.0), dtype, "rope q")
+    assert_close(f64(gk), oracle.rope(f64(kh), pos, 500000.0), dtype, "rope k")
+    assert torch.equal(gv, vh), "rope touched the V columns"
+
+
 # ------------------------------------------------------ KV-cache write ---
 @pytest.mark.parametrize("dtype,T,Hkv,D,bs,nb", [("bf16", 300, 8, 128, 16, 40), ("f32", 50, 2, 64, 1, 80),
                                                  ("bf16", 1, 1, 64, 256, 2)])
