@@ -127,14 +127,15 @@ size_t opscale_linear_workspace_size(int64_t M, int64_t N, int64_t K, opscale_dt
  * x: [M, K]; W: [N, K] (the nn.Linear weight layout); bias: [N] or NULL;
  * y: [M, N], must not alias x or W.  bf16: MFMA with fp32 accumulation.
  * K * sizeof(dt) and N * sizeof(dt) must be multiples of 16.
- * The bf16 path (small-M kernel, decode-batch kernel for 33-128 rows, or a
- * 256x256, 192x256 or 256x128 block tile, with K split over workgroups where
- * that fills the GPU) is chosen per shape.
+ * The bf16 path (small-M kernel, decode-batch kernel for up to 128 rows, or a
+ * 256x256 or 128x256 block tile, with K split over workgroups where that fills
+ * the GPU) is chosen per shape.
  * workspace: NULL, or DEVICE scratch of workspace_bytes, 16-byte aligned, not
  *   overlapping x, W or y.  NULL takes a path that needs none (no K split;
  *   slower for decode-sized M and for a last round of tiles that is mostly
  *   idle).  Non-NULL must hold opscale_linear_workspace_size(M, N, K, dt)
- *   bytes, else OPSCALE_ERR_WORKSPACE with nothing enqueued.  Its contents on
+ *   bytes, else OPSCALE_ERR_WORKSPACE with nothing enqueued (up to 32 rows may
+ *   take the small-M kernel instead, which needs none).  Its contents on
  *   entry are ignored; calls sharing a workspace must be stream-ordered.
  *   Split partials are summed in a fixed order, so results are deterministic.
  */

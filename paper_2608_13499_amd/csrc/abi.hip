@@ -240,6 +240,12 @@ opscale_status check_linear(const void* x, const void* W, const void* bias, void
   // no workspace: a path that needs none; a workspace: the path it allows,
   // which must then fit
   *plan = opscale::plan_linear(M, N, K, dt == OPSCALE_BF16, ws != nullptr);
+  // (a workspace too small for the weight-streaming kernel's K ranges leaves the
+  // rows that the small-M kernel takes without one to that kernel)
+  if (ws_bytes < plan->ws_bytes && opscale::tuning(OPSCALE_TUNE_GEMM_DECODE) != 1) {
+    const opscale::LinearPlan bare = opscale::plan_linear(M, N, K, dt == OPSCALE_BF16, false);
+    if (bare.path == opscale::LinearPlan::kSkinny) *plan = bare;
+  }
   if (plan->ws_bytes > 0) {
     if (ws_bytes < plan->ws_bytes)
       return fail(OPSCALE_ERR_WORKSPACE, "linear: workspace of %zu bytes, %zu needed", ws_bytes, plan->ws_bytes);

@@ -229,6 +229,24 @@ def test_linear_decode_batch_shapes(ops, tune, M, N, K, bias):
     assert_close(f64(y.cpu()), ref, "bf16", "linear")
 
 
+@pytest.mark.parametrize("M", [8, 16, 32])
+def test_linear_small_m_workspace_too_small(ops, M):
+    """Rows that the small-M kernel takes without a workspace still run with
+    one too small for the weight-streaming kernel's K ranges, on the path that
+    takes none; more rows than that are refused."""
+    import torch
+    N, K = 6144, 4096
+    assert ops.opscale_linear_workspace_size(M, N, K) > 16
+    say(f"linear bf16 small-M with a small workspace M={M}")
+    x, W = cuda(gen(34, "x", (64, K), "bf16")), cuda(gen(34, "w_qkv", (N, K), "bf16", std=0.02))
+    ws = torch.zeros(16, dtype=torch.uint8, device="cuda")
+    y = ops.opscale_linear(x[:M], W, workspace=ws)
+    assert torch.equal(y, ops.opscale_linear(x[:M], W, workspace=False))
+    with pytest.raises(ops.OpscaleError) as e:
+        ops.opscale_linear(x, W, workspace=ws)
+    assert e.value.status == ops.OPSCALE_ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("M,N,K,bias", [
     (129, 264, 64, True), (130, 8, 200, False), (256, 520, 128, True), (385, 1032, 192, False), (257, 2056, 1000, True),
     (140, 5000, 1096, False), (256, 4096, 2048, True), (300, 776, 3080, True), (512, 4104, 4096, False),
