@@ -27,6 +27,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "gemm_schedule.h"
 #include "common.h"
 #include "launch.h"
 
@@ -34,7 +35,6 @@ namespace opscale {
 
 namespace {
 
-constexpr int kNumCUs = 256;  // MI355X compute units
 constexpr int64_t kGroupBytes = (int64_t)16 << 20;  // x rows per tile group (see tile_group_rows)
 constexpr int64_t kW4MaxN = (int64_t)1 << 22;  // the four-wave kernel's 32-bit offsets into 256 rows of y
 constexpr int64_t kSplitKMaxM = 2048;  // split-K is for small M (decode batches)
@@ -583,19 +583,17 @@ __device__ __forceinline__ void pin_v(V& v) {
 // first k-step of slice s (into the buffer slice s - 1 freed), the other
 // operand's during the second, so 1 to 1.5 slices are in flight per CU.
 //
-// A workgroup runs a chain of up to kChain tiles: the loads run on into the
+// A workgroup runs a chain of up to kMaxChain tiles: the loads run on into the
 // next tile's first slices while the last ones of this tile are used, and the
 // stores of a tile drain under the next one's first slice.  A tile of its own
 // pays the first loads' latency and the drain each time (about 10 of the 93
-// us of a K = 4096 tile; gate-up 1532 -> 1497 us, QKV 343 -> 338, O 234 -> 232,
-// long K unchanged).  The chain is short so that a launch on a CU-masked
-// stream, or beside other work, still balances over whatever CUs it gets.
+// us of a K = 4096 tile).  Chains shorten towards the end of a launch, so that
+// it balances over whatever CUs it gets (gemm_schedule.h).
 //
 // The columns of a W fragment pair are interleaved in runs of four (fragment
 // i, row f: column 32 (i / 2) + 8 (f / 4) + 4 (i & 1) + f % 4), so a lane's
 // two accumulators hold eight consecutive columns: one 16-byte store.  The W
 // rows are swizzled by that row's place in the fragment, as the x rows are.
-constexpr int kChain = 4;
 template <class C, bool XLEAD, bool RAGGED_K, bool GROUPED>
 __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf16* __restrict__ x,
                                                                       const __bf16* __restrict__ W,
@@ -604,7 +602,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
                                                                       int K_total, int group_m, int kchunk,
                                                                       float* __restrict__ part, GroupedGemm gg,
                                                                       int dp_cnt, int tail_cnt, int items,
-                                                                      int chain) {
+                                                                      bool chained) {
   static_assert(C::kWaves == 4 && C::WM == 128 && C::WN == 128 && !C::DEEP, "four waves of 128x128");
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, WM = C::WM, WN = C::WN;
@@ -688,10 +686,10 @@ __global__ __launch_bounds__(C::kThreads, 1) void gemm_bf16_w4_kernel(const __bf
     return it;
   };
 
-  // This workgroup's chain: items id, id + kNumCUs, ... below id_end (a
-  // launch's items run in rounds of kNumCUs, `chain` rounds per workgroup).
-  int id = (int)(blockIdx.x / kNumCUs) * (kNumCUs * chain) + (int)(blockIdx.x % kNumCUs);
-  const int id_end = min(items, (int)(blockIdx.x / kNumCUs + 1) * (kNumCUs * chain));
+  // This workgroup's chain: items id, id + kNumCUs, ... below id_end.
+  const Chain ch = chain_of((int)(blockIdx.x / kNumCUs), (items + kNumCUs - 1) / kNumCUs, chained);
+  int id = ch.first * kNumCUs + (int)(blockIdx.x % kNumCUs);
+  const int id_end = min(items, (ch.first + ch.len) * kNumCUs);
   if (id >= id_end) return;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1425,24 +1423,22 @@ static hipError_t launch_gemm_bf16(const void* x, const void* W, const void* bia
 }
 
 // The same launches on the four-wave kernel: items (tiles, then the K ranges
-// of a split tail, or the ranges of every tile) in rounds of kNumCUs, kChain
-// rounds per workgroup.
+// of a split tail, or the ranges of every tile), chained where `chained`.
 template <bool XLEAD, bool RAGGED_K, bool GROUPED>
 static hipError_t launch_gemm_w4_kernel(const void* x, const void* W, const void* bias, void* y, int64_t M, int64_t N,
                                         int64_t K, int group_m, int64_t kchunk, float* part, int64_t dp, int64_t tail,
-                                        int64_t items, int chain, const GroupedGemm& gg, hipStream_t s) {
+                                        int64_t items, bool chained, const GroupedGemm& gg, hipStream_t s) {
   using C = CfgW4;
   constexpr int kLds = 5 * C::BM * C::kRowBytes;  // five half-slices
   static const hipError_t attr =
       hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K, GROUPED>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
-  const int64_t per = (int64_t)kNumCUs * chain, full = items / per;
-  const int64_t grid = full * kNumCUs + std::min<int64_t>(kNumCUs, items - full * per);
+  const int64_t grid = chain_grid(items, chained, !GROUPED);
   hipLaunchKernelGGL((gemm_bf16_w4_kernel<C, XLEAD, RAGGED_K, GROUPED>), dim3((unsigned)grid), dim3(C::kThreads), kLds, s,
                      static_cast<const __bf16*>(x), static_cast<const __bf16*>(W), static_cast<const __bf16*>(bias),
                      static_cast<__bf16*>(y), (int)M, (int)N, (int)K, group_m, (int)kchunk, part, gg, (int)dp,
-                     (int)tail, (int)items, chain);
+                     (int)tail, (int)items, chained);
   return hipGetLastError();
 }
 
@@ -1458,7 +1454,7 @@ static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias,
   const int64_t items = tail ? dp + tail * nsplit : tiles * nsplit;
   // the kernel's load cursors run two slices ahead, into the next item only:
   // items of fewer than three slices are not chained
-  const int chain = K - (nsplit - 1) * kchunk > 2 * C::BK ? kChain : 1;
+  const bool chained = K - (nsplit - 1) * kchunk > 2 * C::BK;
   // The ring gives half a slice more of lead to one operand: the one with
   // fewer distinct blocks among the 32 tiles an XCD runs at once (x when a
   // group spans at most 4 tile-rows, i.e. K >= 8192; W for the 8-row groups of
@@ -1468,7 +1464,7 @@ static hipError_t launch_gemm_w4(const void* x, const void* W, const void* bias,
   const bool xlead = group_m <= 4, ragged = K % C::BK != 0;
   const auto go = [&](auto xl, auto rk) {
     return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value, false>(
-        x, W, bias, y, M, N, K, group_m, kchunk, sp > 1 ? part : nullptr, tail ? dp : 0, tail, items, chain,
+        x, W, bias, y, M, N, K, group_m, kchunk, sp > 1 ? part : nullptr, tail ? dp : 0, tail, items, chained,
         GroupedGemm{}, s);
   };
   using T = std::true_type;
@@ -1585,7 +1581,7 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
     const GroupedGemm gg{gather, rows, tiles, E, (int)x_rows, w_stride, swiglu_f};
     const auto go = [&](auto xl, auto rk) {
       return launch_gemm_w4_kernel<decltype(xl)::value, decltype(rk)::value, true>(
-          x, W, nullptr, y, max_rows, N, K, 1, K, nullptr, 0, 0, items, kChain, gg, s);
+          x, W, nullptr, y, max_rows, N, K, 1, K, nullptr, 0, 0, items, true, gg, s);
     };
     using T = std::true_type;
     using F = std::false_type;

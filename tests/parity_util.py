@@ -78,3 +78,18 @@ def f64(t) -> np.ndarray:
 
 def cuda(t):
     return t.to("cuda")
+
+
+def linear_plan(M, N, K, bf16=True, split_ok=True):
+    """The library's own plan of a linear (csrc/launch.h, LinearPlan)."""
+    import ctypes
+
+    import paper_2608_13499_amd as ops
+
+    class Plan(ctypes.Structure):
+        _fields_ = [("path", ctypes.c_int), ("cfg", ctypes.c_int), ("splits", ctypes.c_int),
+                    ("tail_splits", ctypes.c_int), ("ws_bytes", ctypes.c_size_t)]
+
+    f = ops.load()._ZN7opscale11plan_linearElllbb
+    f.restype, f.argtypes = Plan, [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2
+    return f(M, N, K, bf16, split_ok)

@@ -96,16 +96,60 @@ def test_fused_moe_sort_sizes(ops, T, E, k):
 @pytest.mark.parametrize("fuse", [-1, 0])
 @pytest.mark.parametrize("T,H,F,E,k", [(1500, 264, 4096, 4, 2), (700, 192, 8200, 2, 2), (1200, 136, 1032, 9, 1)])
 def test_fused_moe_chained_tiles(ops, tune, fuse, T, H, F, E, k):
-    """Batches of more than 64 rows an expert run on the four-wave kernel, more
-    256x256 tiles than one round of the CUs as chains that cross from expert to
-    expert: a partial last K slice on either side, K of three slices, K past
-    8192 (x in the lead), rows of no expert, ragged tile-rows."""
+    """Batches of more than 64 rows an expert run on the four-wave kernel: a
+    partial last K slice on either side, K of three slices, K past 8192 (x in the
+    lead), rows of no expert, ragged tile-rows.  (Fewer tiles than it chains: the
+    test after this one.)"""
     tune(moe_fuse=fuse)
-    say(f"fused_moe chained tiles T={T} H={H} F={F} E={E} topk={k} fuse={fuse}")
+    say(f"fused_moe four-wave tiles T={T} H={H} F={F} E={E} topk={k} fuse={fuse}")
     ids = np.random.default_rng(T).integers(0, E, size=(T, k))
     ids[::53, 0] = -1
     got, ref = _moe_case(ops, T, H, F, E, k, seed=T + F, ids=ids)
-    assert_close(got, ref, "bf16", "fused_moe chained tiles")
+    assert_close(got, ref, "bf16", "fused_moe four-wave tiles")
+
+
+@pytest.mark.parametrize("fuse", [-1, 0])
+@pytest.mark.parametrize("T,H,F,E,k,chained", [
+    (2500, 136, 12808, 9, 1, "gate_up"),   # ragged K of two slices and a part, in chains
+    (2500, 192, 12808, 9, 1, "gate_up"),   # K of three slices
+    (11000, 4096, 8200, 6, 2, "both"),     # gate-up in 22 rounds; down with x in the lead, ragged
+    (11000, 4096, 8192, 6, 2, "both"),
+])
+def test_fused_moe_chains_over_experts(ops, tune, fuse, T, H, F, E, k, chained):
+    """Six rounds of the CUs' 256x256 tiles and more: the four-wave kernel's
+    workgroups run chains of tiles, which cross from an expert's rows and weights
+    to another's; experts of uneven and of no rows, entries of no expert."""
+    import torch
+    tune(moe_fuse=fuse)
+    say(f"fused_moe chains T={T} H={H} F={F} E={E} topk={k} fuse={fuse}")
+    rng = np.random.default_rng(T + F)
+    p = np.arange(1.0, E + 1)
+    p[E // 2] = 0  # an expert without rows
+    ids = rng.choice(E, size=(T, k), p=p / p.sum())
+    ids[::53, 0] = -1
+    tile_rows = int((-(-np.bincount(ids[ids >= 0], minlength=E) // 256)).sum())
+    assert T * k > 64 * E and tile_rows * -(-2 * F // 256) > 5 * 256
+    assert chained == "gate_up" or tile_rows * -(-H // 256) > 5 * 256
+    g = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s, std=1.0: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    x, w1, w2 = normal(T, H), normal(E, 2 * F, H, std=H ** -0.5), normal(E, H, F, std=F ** -0.5)
+    idd = torch.from_numpy(ids.astype(np.int32)).cuda()
+    wts = torch.empty(T, k, device="cuda").uniform_(0.1, 1.0, generator=g)
+    out = ops.opscale_fused_moe(x, w1, w2, idd, wts)
+    assert torch.equal(out, ops.opscale_fused_moe(x, w1, w2, idd, wts))
+    ref = torch.zeros(T, H, device="cuda")
+    for e in range(E):
+        rows, slot = torch.nonzero(idd == e, as_tuple=True)
+        if len(rows):
+            gu = x[rows].float() @ w1[e].float().t()
+            act = torch.nn.functional.silu(gu[:, :F]) * gu[:, F:]
+            ref.index_put_((rows,), wts[rows, slot][:, None] * (act @ w2[e].float().t()), accumulate=True)
+    torch.cuda.synchronize()
+    # (a token whose entries are all of no expert is zero on both sides)
+    live = (idd >= 0).any(1).cpu().numpy()
+    got, ref = out.float().cpu().numpy(), ref.cpu().numpy()
+    assert not got[~live].any()
+    assert_close(got[live], ref[live], "bf16", "fused_moe chains")
 
 
 def test_fused_moe_one_hot_expert(ops):

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from parity_util import assert_close, cuda, f64, gen, say, torch_dtype
+from parity_util import assert_close, cuda, f64, gen, linear_plan, say, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -298,22 +298,30 @@ def test_linear_four_and_eight_waves_agree(ops, tune, M, N, K, bias):
     assert_close(f64(y4.cpu()), oracle.linear(f64(x), f64(W), None if b is None else f64(b)), "bf16", "linear")
 
 
-@pytest.mark.parametrize("M,N,K,bias", [(4300, 8200, 192, True), (4300, 8200, 136, False), (4300, 8200, 128, True),
-                                        (9000, 8456, 320, True), (5200, 5000, 1032, True)])
-def test_linear_chained_tiles(ops, tune, M, N, K, bias):
-    """More 256x256 tiles than one round of the CUs: a workgroup of the
-    four-wave kernel runs a chain of them (561 to 1224 tiles: chains of three
-    and four, the last one ragged), the next tile's first slices loading while
-    the previous one ends.  K of three slices (the fewest chained), of two
-    and a part, of two (not chained: each tile a workgroup), of five, of
-    sixteen and a part; a split tail at the end of a chain; ragged M and N.  Bitwise
-    equal to the eight-wave kernel, which runs one tile per workgroup."""
+@pytest.mark.parametrize("M,N,K,bias,tail", [
+    (4300, 8200, 192, True, 0), (4300, 8200, 136, False, 0), (9000, 22000, 128, True, 0), (9000, 8456, 320, True, 0),
+    (5200, 5000, 1032, True, 0), (4300, 4104, 2056, True, 4), (9000, 22000, 192, True, 0), (9200, 11000, 136, False, 0),
+    (9000, 11000, 1032, True, 2), (16900, 5000, 8200, True, 4), (20736, 4096, 8256, False, 4),
+])
+def test_linear_chained_tiles(ops, tune, M, N, K, bias, tail):
+    """More 256x256 tiles than one round of the CUs: from six rounds on a
+    workgroup of the four-wave kernel runs a chain of them, the next tile's first
+    slices loading while the previous one ends.  289 to 1224 tiles in two to five
+    rounds (each tile a workgroup); 1344 to 1560 in six or seven (chains of two
+    to single items); 3096 in 13 (chains of four to one).  K of three slices (the
+    fewest chained), of two and a part, of two (never chained), of five, of
+    sixteen and a part, past 8192 and ragged (x in the lead); a last round split
+    over K in front of which chains end; ragged M and N.  Bitwise equal to the
+    eight-wave kernel, which runs one tile per workgroup."""
     import torch
-    say(f"linear bf16 chained tiles M={M} N={N} K={K} bias={bias}")
-    x = gen(29, "x", (M, K), "bf16")
-    W = gen(29, "w_qkv", (N, K), "bf16", std=0.02)
-    b = gen(29, "bias", (N,), "bf16") if bias else None
-    args = (cuda(x), cuda(W), None if b is None else cuda(b))
+    say(f"linear bf16 chained tiles M={M} N={N} K={K} bias={bias} tail={tail}")
+    tune(gemm_tile=TILES["256x256"])
+    assert linear_plan(M, N, K).tail_splits == tail
+    g = torch.Generator(device="cuda").manual_seed(29)
+    normal = lambda *s, std=1.0: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    x, W = normal(M, K), normal(N, K, std=0.02)
+    b = normal(N) if bias else None
+    args = (x, W, b)
     got = []
     for tile in ("256x256", "256x256", "256x256w8"):
         tune(gemm_tile=TILES[tile])
@@ -321,9 +329,11 @@ def test_linear_chained_tiles(ops, tune, M, N, K, bias):
     torch.cuda.synchronize()
     assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
     assert torch.equal(got[0].view(torch.int16), got[2].view(torch.int16))
-    rows = np.unique(np.r_[0:M:97, 255:M:256, M - 1])
-    ref = oracle.linear(f64(x[rows]), f64(W), None if b is None else f64(b))
-    assert_close(f64(got[0].cpu()[rows]), ref, "bf16", "linear chained")
+    rows = torch.from_numpy(np.unique(np.r_[0:M:397, 255:M:512, M - 1])).cuda()
+    ref = x[rows].double() @ W.double().t()
+    if b is not None:
+        ref += b.double()
+    assert_close(got[0][rows].double().cpu().numpy(), ref.cpu().numpy(), "bf16", "linear chained")
 
 
 @pytest.mark.parametrize("tile,M,N,K,bias", [("256x256", 4352, 4096, 1024, True), ("256x256", 4300, 4104, 2056, False),
