@@ -29,6 +29,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "attn_f32_plan.h"
 #include "common.h"
 #include "launch.h"
 
@@ -380,22 +381,64 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_bf16_kernel(
 // number of workgroups, hence the keys over the waves.  One prompt of 128, four
 // heads of 64: 7.9 us; one wave per (token, head) with a key per lane, each
 // lane walking its own K row, took 15.4.
-template <int D>
-__global__ __launch_bounds__(256) void attn_prefill_f32_kernel(
+//
+// Item i is head i % Hq of tile i / Hq.  The heads are innermost, so a KV head's
+// keys stay in few XCDs' L2 (2048 tokens, 32 heads of 128: 619 -> 433 us), and
+// the longest tiles come first.  LIST: i / Hq counts the tiles of the prompts of
+// more than min_len tokens; each wave finds its tile's prompt from cu_seqlens, 64
+// prompts at a time.  Otherwise prompts of about one length: tile j is row j / B
+// of prompt j % B, counted from the last of `levels`, no search.
+template <int D, bool LIST>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     int64_t q_stride, int64_t kv_stride, float* __restrict__ o, const int32_t* __restrict__ cu,
-    int Hq, int Hkv, int levels, float scale, int causal) {
+    int B, int Hq, int Hkv, int64_t items, int levels, int min_len, float scale, int causal) {
   constexpr int DC = D / 8, DT = D / 32;  // chunk pairs of a row, 32-wide output tiles
   constexpr int kCols = 64, kPad = kCols + 4;  // the merge takes 64 columns at a time
   __shared__ __attribute__((aligned(16))) float os[4][32][kPad];
   __shared__ float ms[4][32], ls[4][32];
   const int lane = threadIdx.x & 63, fr = lane & 31, fh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bh = blockIdx.x / levels, level = blockIdx.x % levels;
-  const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hkv);
-  const int seq0 = cu[b], L = cu[b + 1] - seq0;
-  // (longest first, as many tiles as levels apart if the prompt has more)
-  for (int t = levels - 1 - level; t * 32 < L; t += levels) {
+  int64_t past = 0;  // tiles past the caller's bound, for a prompt that has some
+  for (int64_t item = blockIdx.x; item < items;) {
+    const int h = (int)(item % Hq);
+    int seq0 = 0, L = 0, t = -1;
+    if constexpr (LIST) {
+      int slot = (int)(item / Hq);
+      for (int b0 = 0; b0 < B; b0 += 64) {
+        const int b = min(b0 + lane, B - 1);
+        const int first = cu[b], len = cu[b + 1] - first;
+        const int n = b0 + lane < B && len > min_len ? (len + 31) >> 5 : 0;
+        const int total = wave_sum_i(n);
+        if (slot >= total) {
+          slot -= total;
+          continue;
+        }
+        int end = n;  // inclusive scan over the lanes
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const int u = __shfl_up(end, d, 64);
+          if (lane >= d) end += u;
+        }
+        const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(end > slot));
+        seq0 = __builtin_amdgcn_readlane(first, src);
+        L = __builtin_amdgcn_readlane(len, src);
+        t = __builtin_amdgcn_readlane(end, src) - 1 - slot;
+        break;
+      }
+      if (t < 0) return;  // past the last tile (the list's length is an upper bound)
+      item += gridDim.x;
+    } else {
+      const int j = (int)(item / Hq), b = j % B;
+      seq0 = cu[b];
+      L = cu[b + 1] - seq0;
+      const int64_t tile = levels - 1 - j / B + past;
+      past = (tile + levels) * 32 < L ? past + levels : 0;
+      if (past == 0) item += gridDim.x;
+      if (tile * 32 >= L) continue;
+      t = (int)tile;
+    }
+    const int g = h / (Hq / Hkv);
     const int qi = t * 32 + fr;  // this lane's query
     const float* qrow = q + (int64_t)(seq0 + min(qi, L - 1)) * q_stride + (int64_t)h * D;
     f32x4 qf[DC];
@@ -528,24 +571,85 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(
   }
 }
 
+// Short prompts: one wave per (token, head).  Lane j scores key kv0 + j;
+// probabilities go through LDS and each lane accumulates D/64 output columns.
+// A 32-query tile costs the matrix instructions the same whatever it holds,
+// here a token costs its own keys (attn_f32_plan.h has the line between them).
+template <int D>
+__global__ __launch_bounds__(64) void attn_prefill_f32_row_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    int64_t q_stride, int64_t kv_stride, float* __restrict__ o, const int32_t* __restrict__ cu,
+    int B, int Hq, int Hkv, int max_len, float scale, int causal) {
+  constexpr int DPL = D / 64;
+  __shared__ float qs[D];
+  __shared__ float ps[64];
+  const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+  // prompt of token t
+  int lo = 0, hi = B;  // cu[lo] <= t < cu[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (cu[mid] <= t) lo = mid; else hi = mid;
+  }
+  const int seq0 = cu[lo], L = cu[lo + 1] - seq0, i = t - seq0;
+  if (L > max_len) return;  // (the whole workgroup)
+  const int g = h / (Hq / Hkv);
+  for (int d = lane; d < D; d += 64) qs[d] = q[(int64_t)t * q_stride + (int64_t)h * D + d];
+  __syncthreads();
+  const int kv_end = causal ? i + 1 : L;
+  float m_run = -INFINITY, l_run = 0.f, acc[DPL] = {};
+  for (int kv0 = 0; kv0 < kv_end; kv0 += 64) {
+    const int j = kv0 + lane;
+    float s = -INFINITY;
+    if (j < kv_end) {
+      const float* kr = k + (int64_t)(seq0 + j) * kv_stride + (int64_t)g * D;
+      float dot = 0.f;
+      for (int d = 0; d < D; ++d) dot = fmaf(qs[d], kr[d], dot);
+      s = dot * scale;
+    }
+    const float m_new = fmaxf(m_run, wave_max(s));
+    const float p = j < kv_end ? expf(s - m_new) : 0.f;
+    const float alpha = expf(m_run - m_new);
+    l_run = l_run * alpha + wave_sum(p);
+    m_run = m_new;
+    ps[lane] = p;
+    __syncthreads();
+    const int n = min(64, kv_end - kv0);
+#pragma unroll
+    for (int c = 0; c < DPL; ++c) {
+      const int d = lane + c * 64;
+      float a = acc[c] * alpha;
+      for (int jj = 0; jj < n; ++jj)
+        a = fmaf(ps[jj], v[(int64_t)(seq0 + kv0 + jj) * kv_stride + (int64_t)g * D + d], a);
+      acc[c] = a;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < DPL; ++c)
+    o[((int64_t)t * Hq + h) * D + lane + c * 64] = acc[c] / l_run;
+}
+
 static hipError_t launch_attn_prefill_f32(const void* q, const void* k, const void* v,
                                           int64_t q_stride, int64_t kv_stride, void* o,
                                           const int32_t* cu, int32_t B, int64_t total_tokens, int32_t max_seqlen,
                                           int32_t Hq, int32_t Hkv, int32_t D, float scale, bool causal,
                                           hipStream_t s) {
-  // a workgroup per (prompt, head, 32-query tile up to max_seqlen); where that
-  // is more than a grid holds, each takes several tiles
-  const int64_t bh = (int64_t)B * Hq;
-  const int64_t longest = std::min<int64_t>(max_seqlen, total_tokens);
-  const int64_t levels = std::max<int64_t>(1, std::min<int64_t>((longest + 31) / 32, 0x7fffffff / bh));
-  const dim3 grid((unsigned)(bh * levels));
-#define OPS_PF32(DD)                                                                                              \
-  hipLaunchKernelGGL((attn_prefill_f32_kernel<DD>), grid, dim3(256), 0, s, static_cast<const float*>(q),          \
-                     static_cast<const float*>(k), static_cast<const float*>(v), q_stride, kv_stride,             \
-                     static_cast<float*>(o), cu, Hq, Hkv, (int)levels, scale, (int)causal)
-  if (D == 128) OPS_PF32(128);
-  else OPS_PF32(64);
-#undef OPS_PF32
+  const AttnF32Plan p = attn_f32_plan(B, total_tokens, max_seqlen, Hq, D);
+  const float *qf = static_cast<const float*>(q), *kf = static_cast<const float*>(k);
+  const float* vf = static_cast<const float*>(v);
+  float* of = static_cast<float*>(o);
+  if (p.row_len > 0) {
+    const dim3 grid((unsigned)total_tokens, (unsigned)Hq);
+    const auto kern = D == 128 ? &attn_prefill_f32_row_kernel<128> : &attn_prefill_f32_row_kernel<64>;
+    hipLaunchKernelGGL(kern, grid, dim3(64), 0, s, qf, kf, vf, q_stride, kv_stride, of, cu, B, Hq, Hkv, p.row_len,
+                       scale, (int)causal);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || p.items == 0) return e;
+  }
+  const auto kern = D == 128 ? (p.levels ? &attn_prefill_f32_kernel<128, false> : &attn_prefill_f32_kernel<128, true>)
+                             : (p.levels ? &attn_prefill_f32_kernel<64, false> : &attn_prefill_f32_kernel<64, true>);
+  hipLaunchKernelGGL(kern, dim3(p.grid), dim3(256), 0, s, qf, kf, vf, q_stride, kv_stride, of, cu, B, Hq, Hkv, p.items,
+                     p.levels, p.row_len, scale, (int)causal);
   return hipGetLastError();
 }
 

@@ -457,11 +457,53 @@ def test_attn_prefill_f32_tiles(ops, lens, Hq, Hkv, D, causal):
     assert_close(got, ref, "f32", "attn_prefill f32")
 
 
+@pytest.mark.parametrize("lens,bound,Hq,Hkv,D,causal", [
+    ([64], None, 4, 2, 64, True), ([40, 3, 64], None, 4, 4, 128, True),          # a wave per token: few tokens
+    ([10] * 30 + [0, 1], None, 8, 2, 64, True), ([16] * 40, None, 6, 2, 128, False),  # ... or short prompts
+    ([33] * 70, None, 2, 1, 64, True), ([70, 64, 65], None, 8, 8, 128, False),   # tiles, as many for every prompt
+    ([40] * 3, 8192, 12, 4, 64, True), ([90] + [17] * 40, None, 4, 2, 128, False),   # a list of tiles
+    ([20] * 63 + [0, 200, 0, 33] + [20] * 70 + [100], None, 4, 4, 64, True),     # ... over three blocks of prompts
+    ([0] * 64 + [500], None, 3, 1, 128, True), ([100, 90, 130, 97], 40, 4, 2, 128, True),  # (a bound that is none)
+    ([1] * 150 + [300, 33, 32, 31] + [2] * 60 + [34], None, 8, 2, 64, True),     # both: up to 32 tokens a wave each
+    ([0, 32, 65] + [3] * 100, 4096, 4, 4, 128, True), ([5] * 300, 2048, 4, 2, 64, False),
+])
+def test_attn_prefill_f32_plans(ops, lens, bound, Hq, Hkv, D, causal):
+    """The fp32 kernels and their work lists, each on batches that take it:
+    tight and loose bounds, empty prompts, skewed lengths."""
+    import torch
+    say(f"attn_prefill f32 plans lens={lens[:4]}... B={len(lens)} bound={bound} Hq={Hq} Hkv={Hkv} D={D} causal={causal}")
+    cu = wl.cu_seqlens(lens)
+    T = int(cu[-1])
+    q, k, v = gen(38, "q", (T, Hq, D), "f32"), gen(38, "k", (T, Hkv, D), "f32"), gen(38, "v", (T, Hkv, D), "f32")
+    out = torch.full((T, Hq, D), float("nan"), device="cuda")
+    ops.opscale_attn_prefill(cuda(q), cuda(k), cuda(v), cuda(torch.from_numpy(cu)), bound or max(lens), D ** -0.5, causal,
+                             out=out)
+    torch.cuda.synchronize()
+    assert_close(f64(out.cpu()), oracle.attn_prefill(f64(q), f64(k), f64(v), cu, D ** -0.5, causal), "f32", "attn f32 plans")
+
+
+def test_attn_prefill_f32_loose_bound_of_many_prompts(ops):
+    """1024 prompts of 20 tokens, 32 heads, under a bound of 16384: as many tiles
+    for every prompt as the bound allows are 2^24 workgroups, more than a grid."""
+    import torch
+    B, L, Hq, Hkv, D = 1024, 20, 32, 1, 64
+    say("attn_prefill f32 loose bound")
+    cu = wl.cu_seqlens([L] * B)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.empty(B * L, h, D, device="cuda").normal_(generator=g) for h in (Hq, Hkv, Hkv))
+    out = ops.opscale_attn_prefill(q, k, v, cuda(torch.from_numpy(cu)), 16384, D ** -0.5)
+    torch.cuda.synchronize()
+    heads = [0, 13, 31]
+    ref = oracle.attn_prefill(f64(q[:, heads].cpu()), f64(k.cpu()), f64(v.cpu()), cu, D ** -0.5, True)
+    assert_close(f64(out[:, heads].cpu()), ref, "f32", "attn f32 loose bound")
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_attn_prefill_f32_future_is_not_read(ops, bad, D):
     """An infinity or NaN in the keys and values of later tokens of the prompt,
-    or of the next prompt, leaves the queries before them unchanged."""
+    or of the next prompt, leaves the queries before them unchanged (prompts long
+    enough for the tiles)."""
     import torch
     say(f"attn_prefill f32 future {bad} D={D}")
     lens, H = [75, 40], 2

@@ -6,6 +6,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -22,9 +23,14 @@ def host(tmp_path_factory):
     src, so = str(d / "launch_shapes.cpp"), str(d / "launch_shapes.so")
     with open(src, "w") as f:
         f.write('''
+#include "attn_f32_plan.h"
 #include "gemm_schedule.h"
 using namespace opscale;
 extern "C" {
+void attn_f32(int64_t B, int64_t T, int64_t longest, int64_t Hq, int64_t D, int64_t* out) {
+  const AttnF32Plan p = attn_f32_plan(B, T, longest, Hq, D);
+  out[0] = p.row_len, out[1] = p.items, out[2] = p.levels, out[3] = p.grid;
+}
 void chain(int group, int rounds, int chained, int* out) {
   const Chain c = chain_of(group, rounds, chained != 0);
   out[0] = c.first, out[1] = c.len;
@@ -36,6 +42,8 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib = ctypes.CDLL(so)
     lib.grid.restype = ctypes.c_int64
     lib.grid.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    lib.attn_f32.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_void_p]
+    lib.attn_f32.restype = None
     return lib
 
 
@@ -101,3 +109,38 @@ def test_long_launches_are_chained(host):
     for items, least in ((3920, 0.5), (8624, 0.6), (2 * 8624, 0.65)):
         wgs = _chains(host, items, host.grid(items, 1, 1))
         assert sum(len(w) - 1 for w in wgs) >= least * items
+
+
+# ------------------------------------------------- fp32 prefill attention ---
+def _attn(host, B, T, longest, Hq, D):
+    out = (ctypes.c_int64 * 4)()
+    host.attn_f32(B, T, longest, Hq, D, out)
+    return list(out)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_attn_f32_plan(host, D):
+    """Whatever the batch and however loose the bound: a launch that HIP takes,
+    with an item for every tile and not many more, or a wave per token where
+    that is one launch for all."""
+    rng = np.random.default_rng(D)
+    cases = [(1024, 1024 * 16, 16384, 32), (128, 131072, 131072, 32), (2048, 2047 * 4 + 8192, 8192, 32),
+             (1, 1 << 26, 1 << 30, 8), (1, 1 << 30, 1 << 30, 1), (1 << 24, 1 << 24, 1, 4), (3000, 3000, 2**31 - 1, 64),
+             (1, 128, 128, 4), (256, 7680, 30, 4), (64, 64, 4096, 4), (1, 1, 1, 1)]
+    for _ in range(3000):
+        B = int(2 ** rng.uniform(0, 12))
+        T = int(B * 2 ** rng.uniform(-2, 12)) + 1
+        cases.append((B, T, min(2**31 - 1, int(-(-T // B) * 2 ** rng.uniform(0, 14))), int(2 ** rng.uniform(0, 7))))
+    for B, T, longest, Hq in cases:
+        row_len, items, levels, grid = _attn(host, B, T, longest, Hq, D)
+        if items == 0:
+            assert row_len == 2**31 - 1 and T * 64 < 2**32
+            continue
+        assert 1 <= grid <= items and grid * 256 < 2**32, (B, T, longest, Hq)
+        assert row_len == 0 or T * 64 < 2**32
+        # at most 2.25 times the tiles that B prompts of T tokens can have, heads each
+        assert items <= 2.25 * (T // 32 + B) * Hq, (B, T, longest, Hq)
+        if levels:
+            assert row_len == 0 and items == B * levels * Hq and levels * 32 >= min(longest, T)
+        else:  # any split of T into B prompts: L // 32 + 1 tiles a prompt of more than row_len tokens
+            assert items >= (T // 32 + min(B, T // (row_len + 1))) * Hq
