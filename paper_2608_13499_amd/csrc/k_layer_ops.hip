@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "grid.h"
 #include "launch.h"
 
 namespace opscale {
@@ -258,15 +259,19 @@ static hipError_t add_rmsnorm_dispatch(const void* x, void* res, const void* w, 
   constexpr int kRows = 4 / WPR;  // rows of a workgroup
   const int64_t nvec = H / (BF16 ? 8 : 4);
   const int vpl = (int)((nvec + 64 * WPR - 1) / (64 * WPR));
-  const dim3 grid((unsigned)((M + kRows - 1) / kRows)), block(256);
   const int h = (int)H;
+  const int64_t row_bytes = H * (BF16 ? 2 : 4);
+  return launch_rows(M, kRows, [&](int64_t m, int64_t rows, uint32_t grid) {
+    const char* xm = static_cast<const char*>(x) + m * row_bytes;
+    char *rm = static_cast<char*>(res) + m * row_bytes, *ym = static_cast<char*>(y) + m * row_bytes;
 #define OPS_ADDRMS(V) \
-  hipLaunchKernelGGL((add_rmsnorm_kernel<BF16, V, WPR>), grid, block, 0, s, x, res, w, y, M, h, eps)
-  if (vpl <= 1) OPS_ADDRMS(1);
-  else if (vpl <= 2) OPS_ADDRMS(2);
-  else if constexpr (WPR > 1) OPS_ADDRMS(4);  // (rows of at most 16 KB)
+  hipLaunchKernelGGL((add_rmsnorm_kernel<BF16, V, WPR>), dim3(grid), dim3(256), 0, s, xm, rm, w, ym, rows, h, eps)
+    if (vpl <= 1) OPS_ADDRMS(1);
+    else if (vpl <= 2) OPS_ADDRMS(2);
+    else if constexpr (WPR > 1) OPS_ADDRMS(4);  // (rows of at most 16 KB)
 #undef OPS_ADDRMS
-  return hipGetLastError();
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_add_rmsnorm(const void* x, void* res, const void* w, void* y, int64_t M, int64_t H, float eps,

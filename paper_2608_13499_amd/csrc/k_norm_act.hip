@@ -3,6 +3,7 @@
 // Both stream their operands once from HBM with 16-byte loads and stores per
 // lane, keep the math in fp32 and round once at the output.
 #include "common.h"
+#include "grid.h"
 #include "launch.h"
 
 namespace opscale {
@@ -98,19 +99,24 @@ static hipError_t rmsnorm_dispatch(const void* x, const void* w, void* y, int64_
   constexpr int kRows = 4 / WPR;  // rows of a workgroup
   const int64_t nvec = H / (BF16 ? 8 : 4);
   const int vpl = (int)((nvec + 64 * WPR - 1) / (64 * WPR));
-  const dim3 grid((unsigned)((M + kRows - 1) / kRows)), block(256);
   const int h = (int)H;
-#define OPS_RMS(V) hipLaunchKernelGGL((rmsnorm_kernel<BF16, V, WPR>), grid, block, 0, s, x, w, y, M, h, eps)
-  if (vpl <= 1) OPS_RMS(1);
-  else if (vpl <= 2) OPS_RMS(2);
-  else if constexpr (WPR > 1) {
-    if (vpl <= 4) OPS_RMS(4);
-    else if (vpl <= 8) OPS_RMS(8);
-    else if (vpl <= 16) OPS_RMS(16);
-    else OPS_RMS(0);
-  }
+  const int64_t row_bytes = H * (BF16 ? 2 : 4);
+  return launch_rows(M, kRows, [&](int64_t m, int64_t rows, uint32_t grid) {
+    const char* xm = static_cast<const char*>(x) + m * row_bytes;
+    char* ym = static_cast<char*>(y) + m * row_bytes;
+#define OPS_RMS(V) \
+  hipLaunchKernelGGL((rmsnorm_kernel<BF16, V, WPR>), dim3(grid), dim3(256), 0, s, xm, w, ym, rows, h, eps)
+    if (vpl <= 1) OPS_RMS(1);
+    else if (vpl <= 2) OPS_RMS(2);
+    else if (vpl <= 4) OPS_RMS(4);
+    else if constexpr (WPR > 1) {
+      if (vpl <= 8) OPS_RMS(8);
+      else if (vpl <= 16) OPS_RMS(16);
+      else OPS_RMS(0);
+    }
 #undef OPS_RMS
-  return hipGetLastError();
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int64_t H, float eps,

@@ -157,6 +157,32 @@ def test_norm_row_lengths(ops, dtype, H):
         assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, f"rmsnorm H={long}")
 
 
+def test_norms_past_one_grid(ops):
+    """2^24 + 3 rows of a workgroup each: more workgroups of 256 threads than a
+    grid holds (35 GB a tensor; both norms in place of y or of the residual)."""
+    import torch
+    M, H, P = 2**24 + 3, 1032, 4099  # P: rows repeat with a period that divides nothing
+    if torch.cuda.mem_get_info()[0] < 80e9:
+        pytest.skip("needs 80 GB of free GPU memory")
+    say(f"norms M={M} H={H}")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    base, w = (torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(1.0, 0.5, generator=g) for s in ((P, H), (H,)))
+    x = torch.empty(M, H, dtype=torch.bfloat16, device="cuda")
+    for i in range(0, M, P):
+        x[i:i + P] = base[:min(P, M - i)]
+    rows = torch.tensor([0, 1, 2**24 - 2, 2**24 - 1, 2**24, M - 1], device="cuda")
+    ref = oracle.rmsnorm(f64(base[rows % P].cpu()), f64(w.cpu()), 1e-5)
+    r = x.clone()
+    y = ops.opscale_add_rmsnorm(x, r, w, eps=1e-5, y=x)  # residual 2 x, y in place of x
+    torch.cuda.synchronize()
+    assert_close(f64(y[rows].cpu()), ref, "bf16", "add_rmsnorm")
+    assert torch.equal(r[rows], 2 * base[rows % P])
+    del x, y
+    z = ops.opscale_rmsnorm(r, w, y=r, eps=1e-5)
+    torch.cuda.synchronize()
+    assert_close(f64(z[rows].cpu()), ref, "bf16", "rmsnorm")
+
+
 # ----------------------------------------------------------- a whole layer ---
 def _layer_weights(seed, shape, dtype):
     H, Hq, Hkv, D, F = shape.hidden, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.ffn

@@ -25,11 +25,21 @@ def host(tmp_path_factory):
         f.write('''
 #include "attn_f32_plan.h"
 #include "gemm_schedule.h"
+#include "grid.h"
 using namespace opscale;
 extern "C" {
 void attn_f32(int64_t B, int64_t T, int64_t longest, int64_t Hq, int64_t D, int64_t* out) {
   const AttnF32Plan p = attn_f32_plan(B, T, longest, Hq, D);
   out[0] = p.row_len, out[1] = p.items, out[2] = p.levels, out[3] = p.grid;
+}
+// first row, rows and workgroups of each launch; the number of launches
+int rows(int64_t M, int per_wg, int64_t* out, int most) {
+  int n = 0;
+  launch_rows(M, per_wg, [&](int64_t m, int64_t r, uint32_t grid) {
+    out[3 * n] = m, out[3 * n + 1] = r, out[3 * n + 2] = grid;
+    return ++n == most ? 1 : 0;
+  });
+  return n;
 }
 void chain(int group, int rounds, int chained, int* out) {
   const Chain c = chain_of(group, rounds, chained != 0);
@@ -44,6 +54,7 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib.grid.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     lib.attn_f32.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_void_p]
     lib.attn_f32.restype = None
+    lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
     return lib
 
 
@@ -144,3 +155,21 @@ def test_attn_f32_plan(host, D):
             assert row_len == 0 and items == B * levels * Hq and levels * 32 >= min(longest, T)
         else:  # any split of T into B prompts: L // 32 + 1 tiles a prompt of more than row_len tokens
             assert items >= (T // 32 + min(B, T // (row_len + 1))) * Hq
+
+
+# -------------------------------------------------------- one row a group ---
+@pytest.mark.parametrize("per_wg", [1, 4])
+def test_rows_past_one_grid(host, per_wg):
+    """Rows past what one grid holds go into further launches, each row once."""
+    most = (2**24 - 1) * per_wg
+    for M in (1, 2, 5, 2**24 - 1, 2**24, 2**24 + 5, most - 1, most, most + 1, 2 * most, 2 * most + 3, 2**31 - 1):
+        out = (ctypes.c_int64 * 3072)()
+        n = host.rows(M, per_wg, out, 1024)
+        at = 0
+        for i in range(n):
+            m, r, grid = out[3 * i:3 * i + 3]
+            assert m == at and r > 0 and grid * 256 < 2**32 and (grid - 1) * per_wg < r <= grid * per_wg, (M, i)
+            at += r
+        assert at == M
+    # an error ends it
+    assert host.rows(3 * most, per_wg, (ctypes.c_int64 * 9)(), 2) == 2
