@@ -121,7 +121,12 @@ static hipError_t rmsnorm_dispatch(const void* x, const void* w, void* y, int64_
 
 hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int64_t H, float eps,
                           bool bf16, hipStream_t s) {
-  if (H / (bf16 ? 8 : 4) > kWaveRowMaxVec)
+  // rows of up to 255 vectors leave part of a workgroup idle, which shows where
+  // there are rows enough to fill the chip with a wave each (us, wave / workgroup a
+  // row: 1032 wide, 1023 rows 3.27 / 3.27, 2048 4.0 / 4.2, 8871 10.0 / 12.0; 1536
+  // wide, 100 rows 2.57 / 2.44, 20000 22.8 / 24.1; 2048 wide, 20000 30.0 / 29.6)
+  const int64_t nvec = H / (bf16 ? 8 : 4);
+  if (nvec > kWaveRowMaxVec && (nvec >= 256 || M < 2048))
     return bf16 ? rmsnorm_dispatch<true, 4>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 4>(x, w, y, M, H, eps, s);
   return bf16 ? rmsnorm_dispatch<true, 1>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 1>(x, w, y, M, H, eps, s);
 }

@@ -15,7 +15,8 @@ namespace opscale {
 int32_t tuning(opscale_tune knob);
 
 // RMS Norm and residual norm: rows of more than this many 16-byte vectors take
-// a workgroup each, shorter ones a wave (a workgroup would have idle lanes).
+// a workgroup each, shorter ones a wave (a workgroup would have idle lanes; so do
+// large batches of not much longer rows in the RMS Norm, launch_rmsnorm).
 // A whole row in one wave is one chain of loads, reduction and stores, and few
 // rows leave most of the chip idle.  Measured (us, H = 4096, wave / workgroup
 // per row, residual norm): 3.0 / 2.0 for one row, 3.5 / 2.3 for 48, 8.2 / 7.1

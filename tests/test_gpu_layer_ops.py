@@ -157,6 +157,18 @@ def test_norm_row_lengths(ops, dtype, H):
         assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, f"rmsnorm H={long}")
 
 
+@pytest.mark.parametrize("M,H", [(2047, 1032), (2048, 1032), (2049, 1544), (2048, 2040), (2048, 2048)])
+def test_rmsnorm_many_short_rows(ops, M, H):
+    """Rows of 129 to 255 vectors: a workgroup each up to 2047 of them, a wave
+    each from 2048 on."""
+    import torch
+    say(f"rmsnorm M={M} H={H}")
+    x, w = gen(39, "x", (M, H), "bf16"), gen(39, "w_norm", (H,), "bf16", std=0.02, mean=1.0)
+    z = ops.opscale_rmsnorm(cuda(x), cuda(w), eps=1e-5)
+    torch.cuda.synchronize()
+    assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), "bf16", "rmsnorm")
+
+
 def test_norms_past_one_grid(ops):
     """2^24 + 3 rows of a workgroup each: more workgroups of 256 threads than a
     grid holds (35 GB a tensor; both norms in place of y or of the residual)."""
