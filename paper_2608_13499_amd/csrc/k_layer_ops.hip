@@ -25,9 +25,11 @@ constexpr double kTwoPi = 6.283185307179586476925286766559;
 // stores: each of the D/2 angles is computed once, by one thread, while the
 // rows are on their way, rather than by every head after them (us, 32 + 8 heads
 // of 128, each angle per head / once: one token 3.2 / 2.1, 256 3.9 / 2.7, 1023
-// 6.3 / 4.9, 8871 36.0 / 34.2; 64 + 8 heads, one token 4.4 / 2.8).
-template <bool BF16, int D>
-__global__ __launch_bounds__(256) void rope_kernel(void* q, void* k, int64_t q_stride, int64_t k_stride,
+// 6.3 / 4.9, 8871 36.0 / 34.2; 64 + 8 heads, one token 4.4 / 2.8).  NT: 64 threads
+// a token where they hold its heads at once, 256 otherwise (us, 256 / 64 threads:
+// 4 + 4 heads of 64, 20000 tokens 15.6 / 9.5; 8 + 8, 8871 11.5 / 7.8).
+template <bool BF16, int D, int NT>
+__global__ __launch_bounds__(NT) void rope_kernel(void* q, void* k, int64_t q_stride, int64_t k_stride,
                                                    const int32_t* __restrict__ pos, int Hq, int Hkv,
                                                    double log2_theta) {
   constexpr int HALF = D / 2, QUADS = HALF / 4, kPer = 3;  // quads of a thread requested at once
@@ -45,7 +47,8 @@ __global__ __launch_bounds__(256) void rope_kernel(void* q, void* k, int64_t q_s
   auto load = [&](int idx0) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const char* e = row(min(idx0 + i * 256, total - 1));
+      if (idx0 + i * NT >= total) break;
+      const char* e = row(idx0 + i * NT);
       lo[i] = *reinterpret_cast<const V*>(e);
       hi[i] = *reinterpret_cast<const V*>(e + HALF * (BF16 ? 2 : 4));
     }
@@ -61,7 +64,7 @@ __global__ __launch_bounds__(256) void rope_kernel(void* q, void* k, int64_t q_s
   for (int idx0 = threadIdx.x;;) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int idx = idx0 + i * 256;
+      const int idx = idx0 + i * NT;
       if (idx >= total) break;
       const f32x4 cs = *reinterpret_cast<const f32x4*>(cosine + 4 * (idx % QUADS));
       const f32x4 sn = *reinterpret_cast<const f32x4*>(sine + 4 * (idx % QUADS));
@@ -90,7 +93,7 @@ __global__ __launch_bounds__(256) void rope_kernel(void* q, void* k, int64_t q_s
       *reinterpret_cast<V*>(e) = rlo;
       *reinterpret_cast<V*>(e + HALF * (BF16 ? 2 : 4)) = rhi;
     }
-    idx0 += kPer * 256;
+    idx0 += kPer * NT;
     if (idx0 >= total) break;
     load(idx0);
   }
@@ -99,15 +102,26 @@ __global__ __launch_bounds__(256) void rope_kernel(void* q, void* k, int64_t q_s
 hipError_t launch_rope(void* q, void* k, int64_t q_stride, int64_t k_stride, const int32_t* pos, int64_t T,
                        int32_t Hq, int32_t Hkv, int32_t D, double theta, bool bf16, hipStream_t s) {
   const double l2 = std::log2(theta);
-  const dim3 grid((unsigned)T), block(256);
-#define OPS_ROPE(B, DD) \
-  hipLaunchKernelGGL((rope_kernel<B, DD>), grid, block, 0, s, q, k, q_stride, k_stride, pos, Hq, Hkv, l2)
+  // (three quads a lane; the other three waves would only take up places)
+  const bool one = (Hq + Hkv) * (D / 8) <= 3 * 64;
+  const dim3 grid((unsigned)T);
+#define OPS_ROPE(B, DD)                                                                                               \
+  if (one)                                                                                                            \
+    hipLaunchKernelGGL((rope_kernel<B, DD, 64>), grid, dim3(64), 0, s, q, k, q_stride, k_stride, pos, Hq, Hkv, l2);   \
+  else                                                                                                                \
+    hipLaunchKernelGGL((rope_kernel<B, DD, 256>), grid, dim3(256), 0, s, q, k, q_stride, k_stride, pos, Hq, Hkv, l2)
   if (bf16) {
-    if (D == 128) OPS_ROPE(true, 128);
-    else OPS_ROPE(true, 64);
+    if (D == 128) {
+      OPS_ROPE(true, 128);
+    } else {
+      OPS_ROPE(true, 64);
+    }
   } else {
-    if (D == 128) OPS_ROPE(false, 128);
-    else OPS_ROPE(false, 64);
+    if (D == 128) {
+      OPS_ROPE(false, 128);
+    } else {
+      OPS_ROPE(false, 64);
+    }
   }
 #undef OPS_ROPE
   return hipGetLastError();

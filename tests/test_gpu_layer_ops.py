@@ -66,9 +66,11 @@ def test_rope(ops, dtype, T, Hq, Hkv, D, theta, maxpos):
     assert torch.equal(got[0], qkv[0]), "position 0 must be the identity"
 
 
-# A thread requests three quads of pairs at once: head counts at and past the
-# edges of what the workgroup's 768 cover (16 or 8 quads a head).
-@pytest.mark.parametrize("dtype,Hq,Hkv,D", [("bf16", 1, 1, 64), ("bf16", 40, 8, 128), ("bf16", 48, 1, 128),
+# A thread requests three quads of pairs at once (16 or 8 quads a head): head
+# counts at and past the edges of what one wave's 192 and a workgroup's 768 cover.
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [("bf16", 1, 1, 64), ("bf16", 8, 4, 128), ("f32", 12, 1, 128),
+                                            ("f32", 16, 8, 64), ("bf16", 24, 1, 64),
+                                            ("bf16", 40, 8, 128), ("bf16", 48, 1, 128),
                                             ("bf16", 96, 8, 128), ("f32", 96, 1, 64), ("f32", 64, 64, 128)])
 def test_rope_head_counts(ops, dtype, Hq, Hkv, D):
     import torch
