@@ -2,6 +2,7 @@
 // can be checked on the host.
 #pragma once
 
+#include <cmath>
 #include <cstdint>
 
 #ifdef __HIPCC__
@@ -66,6 +67,33 @@ inline int64_t chain_grid(int64_t items, bool chained, bool exact) {
   }
   // (the last group's chains are single items)
   return exact ? (int64_t)(groups - 1) * kNumCUs + items - (int64_t)(rounds - 1) * kNumCUs : (int64_t)groups * kNumCUs;
+}
+
+// The mixture-of-experts GEMMs of decode batches, on tiles of 64 rows and 256 of N
+// columns.
+//
+// Tiles of a launch: `rows` token-slot pairs over E experts, as if routed evenly (the
+// host does not see the routing): experts that get a row, and a second tile for
+// those that get more than 64 (binomial counts, taken as normal).
+inline double grouped_tiles(int64_t rows, int64_t N, int64_t E) {
+  const double used = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows)), mean = rows / used;
+  return used * (1.0 + 0.5 * std::erfc((64.5 - mean) / std::sqrt(2.0 * mean))) * (double)((N + 255) / 256);
+}
+
+// One workgroup of 160 KB per CU with three slices of K in flight, rather than
+// two of 80 KB with one each?  Either way it is the weights that take the time.
+// Alone on its CU the deep ring streams faster (up to 256 tiles, us, two / one per
+// CU: 16 experts 6144 x 2688, 84 tiles 184 / 151; 8 experts of 14336, the 32 tiles
+// of down 349 / 285), but it runs in rounds of 256 tiles where the pairs run in
+// rounds of 512: a remainder of 257 to 511 is one round of pairs, its CUs
+// sharing the bandwidth, and two of the others (294 tiles 289 / 331, 336 394 / 427,
+// 800 473 / 503, 1372 761 / 766), one of up to 256 the reverse (672 563 / 530, 1160
+// 586 / 561, 1280 645 / 629).  The same over 12 expert shapes of 1 to 512 tokens, K of
+// 768 to 14336.  (Weights that fit the last-level cache, e.g. one expert called over and
+// over, go 1-3 us the other way below 130 tiles, 18 at 8 tiles of K = 8192.)
+inline bool grouped_deep_ring(int64_t rows, int64_t N, int64_t E) {
+  const double last = std::fmod(std::round(grouped_tiles(rows, N, E)), 2.0 * kNumCUs);
+  return last > 0 && last <= kNumCUs;
 }
 
 }  // namespace opscale

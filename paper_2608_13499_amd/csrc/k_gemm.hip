@@ -1558,14 +1558,9 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
                                int64_t max_rows, int64_t N, int64_t K, int32_t E, int32_t tile_rows,
                                const int32_t* gather, const int32_t* rows, const int32_t* tiles, int32_t swiglu_f,
                                hipStream_t s) {
-  // Decode batches.  One 160 KB workgroup per CU with three slices in flight,
-  // or two of 80 KB with one each, which overlap one's fill and epilogue with
-  // the other's loads: the deep ring wins while the tiles carry little compute
-  // or K is long (us, two / deep: 64 experts 3584 x 2560, top-8, 1 token 147 / 111,
-  // 256 tokens 669 / 656, 512 762 / 783; 8 experts 4096 x 14336, top-2, 1 token 353 /
-  // 284, 64 629 / 573, 256 700 / 640).
+  // Decode batches: one workgroup per CU with a deep ring, or two with a shallow one.
   if (tile_rows == CfgRow64::BM) {
-    const bool deep = max_rows <= (int64_t)32 * E || K >= 4096;
+    const bool deep = grouped_deep_ring(max_rows, N, E);
     return deep ? launch_grouped<CfgSk64>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f, s)
                 : launch_grouped<CfgRow64>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f,
                                            s);

@@ -41,6 +41,8 @@ int rows(int64_t M, int per_wg, int64_t* out, int most) {
   });
   return n;
 }
+double moe_tiles(int64_t rows, int64_t N, int64_t E) { return grouped_tiles(rows, N, E); }
+int moe_deep(int64_t rows, int64_t N, int64_t E) { return grouped_deep_ring(rows, N, E); }
 void chain(int group, int rounds, int chained, int* out) {
   const Chain c = chain_of(group, rounds, chained != 0);
   out[0] = c.first, out[1] = c.len;
@@ -55,6 +57,8 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib.attn_f32.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_void_p]
     lib.attn_f32.restype = None
     lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
+    lib.moe_tiles.argtypes = lib.moe_deep.argtypes = [ctypes.c_int64] * 3
+    lib.moe_tiles.restype = ctypes.c_double
     return lib
 
 
@@ -120,6 +124,25 @@ def test_long_launches_are_chained(host):
     for items, least in ((3920, 0.5), (8624, 0.6), (2 * 8624, 0.65)):
         wgs = _chains(host, items, host.grid(items, 1, 1))
         assert sum(len(w) - 1 for w in wgs) >= least * items
+
+
+# ------------------------------------- rings of the MoE decode-batch GEMM ---
+def test_grouped_tile_estimate(host):
+    """The estimate against evenly routed lists."""
+    rng = np.random.default_rng(5)
+    for rows, N, E in ((4, 5376, 16), (32, 6144, 16), (56, 5760, 32), (2048, 5120, 64), (512, 4096, 8), (2, 28672, 8),
+                       (256, 16384, 4), (4096, 3584, 64), (1, 512, 1)):
+        tiles = np.mean([(-(-np.bincount(rng.integers(0, E, rows), minlength=E) // 64)).sum() for _ in range(400)])
+        assert host.moe_tiles(rows, N, E) == pytest.approx(tiles * -(-N // 256), rel=0.06), (rows, N, E)
+
+
+def test_grouped_ring_rule(host):
+    """The deep ring where the launch's last round of 512 tiles holds at most 256
+    (E experts of one column block a tile each; every expert gets a row)."""
+    for E, deep in ((1, 1), (84, 1), (250, 1), (262, 0), (336, 0), (500, 0), (520, 1), (760, 1), (780, 0), (1020, 0)):
+        assert host.moe_deep(20 * E, 256, E) == deep, E
+    # exactly 256 past a whole round (1280 tiles): every one of 64 experts has rows
+    assert host.moe_deep(2048, 5120, 64) and not host.moe_deep(2048, 3584, 64)
 
 
 # ------------------------------------------------- fp32 prefill attention ---
