@@ -22,6 +22,7 @@
 //
 // (fp32: k_gemm_f32.hip.)
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -1598,6 +1599,20 @@ static size_t tail_bytes(int bm, int bn, int64_t M, int64_t N, int64_t K, int ta
   return (size_t)split_ranges(K, tail_splits, 64) * (tiles % kNumCUs) * bm * bn * sizeof(float);
 }
 
+// Does the small-M kernel's extra reading of x (from L2, 15 TB/s) cost less than
+// what the streaming kernel adds: a second launch where it splits K, and a
+// twentieth more for the weights (7 TB/s) where the small-M kernel's workgroups of
+// 16 columns fill whole rounds of the CUs?  Measured (us, streaming / small-M): 8192
+// x 8192, M = 3 28.4 / 26.1, 8 28.6 / 30.2; 7168 x 2048, M = 12 11.7 / 10.4; 5120 x 1536, M
+// = 16 8.8 / 7.9, 24 9.0 / 9.6; 4096 x 14336, M = 6 26.4 / 25.8, 8 26.4 / 27.3; 6144 x 4096
+// (one and a half rounds), M = 6 14.5 / 15.6.  (Within 6 % of the better one
+// elsewhere: 57344 x 8192, M = 3 164.5 / 159.7; 7168 x 2048, M = 24 12.6 / 11.9.)
+static bool skinny_estimate(int64_t M, int64_t N, int64_t K, int splits) {
+  const double weights_us = 2.0 * N * K / 7e6, rounds = (double)N / 16 / kNumCUs;
+  const double idle_us = (std::ceil(rounds) / rounds - 1) * weights_us;
+  return (double)M * N * K / 8 / 15e6 + idle_us <= (splits > 1 ? 2.5 : 0.0) + 0.05 * weights_us;
+}
+
 // One rule for the path of a linear, shared by the workspace query and the
 // launch.  split_ok == false (no caller workspace) plans only paths that need
 // none: the small-M kernel or unsplit tiles.
@@ -1631,7 +1646,8 @@ LinearPlan plan_linear(int64_t M, int64_t N, int64_t K, bool bf16, bool split_ok
   }
   const bool streamed = d.path == LinearPlan::kDecode;
   if (force_tile < 0 && skinny != 0 && !(streamed && dec == 1)) {
-    const bool few = streamed ? M <= 2 || (double)M * N * K <= 3.5e7 * d.splits : skinny_linear_preferred(M, N, K);
+    const bool few = streamed ? M <= 2 || (double)M * N * K <= 3.5e7 * d.splits || skinny_estimate(M, N, K, d.splits)
+                              : skinny_linear_preferred(M, N, K);
     if (skinny_linear_supported(M, N, K) && (skinny == 1 || few)) {
       p.path = LinearPlan::kSkinny;
       return p;

@@ -363,3 +363,14 @@ def test_linear_workspace_over_sizes(lib):
     finally:
         lib.opscale_set_tuning(SPLITK, -1)
         lib.opscale_set_tuning(TAIL, -1)
+
+
+def test_linear_plan_at_its_lines(lib):
+    """Which path a linear takes where two are close."""
+    from parity_util import linear_plan
+    SMALL_M, STREAM = 1, 3
+    for m, n, k, path in ((2, 28672, 4096, SMALL_M), (3, 28672, 4096, STREAM), (3, 8192, 8192, SMALL_M),
+                          (6, 8192, 8192, SMALL_M), (8, 8192, 8192, STREAM), (16, 7168, 2048, SMALL_M),
+                          (32, 7168, 2048, STREAM), (16, 5120, 1536, SMALL_M), (24, 5120, 1536, STREAM),
+                          (6, 4096, 14336, SMALL_M), (8, 4096, 14336, STREAM), (6, 6144, 4096, STREAM)):
+        assert linear_plan(m, n, k).path == path, (m, n, k)
