@@ -134,8 +134,8 @@ size_t opscale_linear_workspace_size(int64_t M, int64_t N, int64_t K, opscale_dt
  *   overlapping x, W or y.  NULL takes a path that needs none (no K split;
  *   slower for decode-sized M and for a last round of tiles that is mostly
  *   idle).  Non-NULL must hold opscale_linear_workspace_size(M, N, K, dt)
- *   bytes, else OPSCALE_ERR_WORKSPACE with nothing enqueued (up to 32 rows may
- *   take the small-M kernel instead, which needs none).  Its contents on
+ *   bytes, else OPSCALE_ERR_WORKSPACE with nothing enqueued (up to 32 rows, or
+ *   129 to 256 of more than 16384 columns, may take a path that needs none).  Its contents on
  *   entry are ignored; calls sharing a workspace must be stream-ordered.
  *   Split partials are summed in a fixed order, so results are deterministic.
  */

@@ -240,18 +240,23 @@ opscale_status check_linear(const void* x, const void* W, const void* bias, void
   // no workspace: a path that needs none; a workspace: the path it allows,
   // which must then fit
   *plan = opscale::plan_linear(M, N, K, dt == OPSCALE_BF16, ws != nullptr);
-  // (a workspace too small for the weight-streaming kernel's K ranges leaves the
-  // rows that the small-M kernel takes without one to that kernel)
-  if (ws_bytes < plan->ws_bytes && opscale::tuning(OPSCALE_TUNE_GEMM_DECODE) != 1) {
+  const auto ws_overlaps = [&] {
+    const int64_t nb = (int64_t)plan->ws_bytes;
+    return overlap(ws, nb, y, M * N * s) || overlap(ws, nb, x, M * K * s) || overlap(ws, nb, W, N * K * s);
+  };
+  // (a workspace that the plan's K ranges cannot use: rows that the small-M kernel
+  // takes without one are left to it, and 129 to 256 rows whose 128-row tiles fill
+  // more than half of the CUs run whole)
+  if (plan->ws_bytes > 0 && (ws_bytes < plan->ws_bytes || !aligned16(ws) || ws_overlaps()) &&
+      opscale::tuning(OPSCALE_TUNE_GEMM_DECODE) != 1) {
     const opscale::LinearPlan bare = opscale::plan_linear(M, N, K, dt == OPSCALE_BF16, false);
-    if (bare.path == opscale::LinearPlan::kSkinny) *plan = bare;
+    if (bare.path == opscale::LinearPlan::kSkinny || (M > 128 && M <= 256 && N > 64 * 256)) *plan = bare;
   }
   if (plan->ws_bytes > 0) {
     if (ws_bytes < plan->ws_bytes)
       return fail(OPSCALE_ERR_WORKSPACE, "linear: workspace of %zu bytes, %zu needed", ws_bytes, plan->ws_bytes);
     if (!aligned16(ws)) return fail(OPSCALE_ERR_INVALID_ARG, "linear: workspace must be 16-byte aligned");
-    if (overlap(ws, (int64_t)plan->ws_bytes, y, M * N * s) || overlap(ws, (int64_t)plan->ws_bytes, x, M * K * s) ||
-        overlap(ws, (int64_t)plan->ws_bytes, W, N * K * s))
+    if (ws_overlaps())
       return fail(OPSCALE_ERR_INVALID_ARG, "linear: workspace overlaps x, W or y");
   }
   return OPSCALE_OK;

@@ -365,6 +365,24 @@ def test_linear_workspace_over_sizes(lib):
         lib.opscale_set_tuning(TAIL, -1)
 
 
+def test_linear_takes_what_needs_no_workspace(lib):
+    """Rows that have a path without a workspace take it where the given one is
+    too small, misaligned or overlaps y: the call gets past its checks (and
+    fails on the device, which is not there); more rows are refused as before."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up addresses: only where nothing can run on them")
+    f, size = lib.opscale_linear, lib.opscale_linear_workspace_size
+    x, W, y, ws = G, 2 * G, 3 * G, 4 * G
+    for m, n, k in ((8, 6144, 4096), (16, 6144, 4096), (32, 6144, 4096), (12, 8192, 28672), (253, 24024, 21312)):
+        assert size(m, n, k, 1) > 16
+        for w, nb in ((ws, 16), (ws + 4, 1 << 30), (y, 1 << 30), (ws, 1 << 30)):
+            assert f(x, W, None, y, m, n, k, 1, w, nb, None, None) == 4, (m, n, k, w - ws, nb)
+    for m, n, k in ((64, 6144, 4096), (256, 6144, 4096)):
+        for (w, nb), st in (((ws, 16), 3), ((ws + 4, 1 << 30), 1), ((y, 1 << 30), 1), ((ws, 1 << 30), 4)):
+            assert f(x, W, None, y, m, n, k, 1, w, nb, None, None) == st, (m, n, k, w - ws, nb)
+
+
 def test_linear_plan_at_its_lines(lib):
     """Which path a linear takes where two are close."""
     from parity_util import linear_plan

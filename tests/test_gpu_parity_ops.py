@@ -242,6 +242,8 @@ def test_linear_small_m_workspace_too_small(ops, M):
     ws = torch.zeros(16, dtype=torch.uint8, device="cuda")
     y = ops.opscale_linear(x[:M], W, workspace=ws)
     assert torch.equal(y, ops.opscale_linear(x[:M], W, workspace=False))
+    big = torch.zeros(ops.opscale_linear_workspace_size(M, N, K) + 16, dtype=torch.uint8, device="cuda")
+    assert torch.equal(y, ops.opscale_linear(x[:M], W, workspace=big[4:])), "a misaligned one"
     with pytest.raises(ops.OpscaleError) as e:
         ops.opscale_linear(x, W, workspace=ws)
     assert e.value.status == ops.OPSCALE_ERR_WORKSPACE
