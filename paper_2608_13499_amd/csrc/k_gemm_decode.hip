@@ -211,7 +211,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_decode_bf16_kernel(const __bf
 }
 
 bool decode_linear_supported(int64_t M, int64_t N, int64_t K) {
-  return M >= 1 && M <= kDecodeMaxM && K % kBK == 0 && N >= 1 && K <= (1 << 20);
+  // (four threads a column: a grid holds fewer than 2^32)
+  return M >= 1 && M <= kDecodeMaxM && K % kBK == 0 && N >= 1 && N < ((int64_t)1 << 30) && K <= (1 << 20);
 }
 
 namespace {

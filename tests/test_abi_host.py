@@ -384,11 +384,12 @@ def test_linear_takes_what_needs_no_workspace(lib):
 
 
 def test_linear_plan_at_its_lines(lib):
-    """Which path a linear takes where two are close."""
+    """Which path a linear takes where two are close, and past a grid's limit."""
     from parity_util import linear_plan
-    SMALL_M, STREAM = 1, 3
+    SMALL_M, TILED, STREAM = 1, 2, 3
     for m, n, k, path in ((2, 28672, 4096, SMALL_M), (3, 28672, 4096, STREAM), (3, 8192, 8192, SMALL_M),
                           (6, 8192, 8192, SMALL_M), (8, 8192, 8192, STREAM), (16, 7168, 2048, SMALL_M),
                           (32, 7168, 2048, STREAM), (16, 5120, 1536, SMALL_M), (24, 5120, 1536, STREAM),
-                          (6, 4096, 14336, SMALL_M), (8, 4096, 14336, STREAM), (6, 6144, 4096, STREAM)):
+                          (6, 4096, 14336, SMALL_M), (8, 4096, 14336, STREAM), (6, 6144, 4096, STREAM),
+                          (40, (1 << 30) - 8, 64, STREAM), (40, 1 << 30, 64, TILED)):
         assert linear_plan(m, n, k).path == path, (m, n, k)
