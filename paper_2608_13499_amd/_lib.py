@@ -234,6 +234,20 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+def _scratch(nbytes, like, stream):
+    """A temporary workspace on `like`'s device for a call on `stream`.  torch
+    may hand its memory on as soon as it is dropped, to work on the current
+    stream: on another one it is kept until that stream's work is done."""
+    import torch
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    if stream is not None:
+        handle = _stream(stream)
+        if handle != _stream(None):
+            ws.record_stream(torch.cuda.ExternalStream(handle, device=like.device) if handle
+                             else torch.cuda.default_stream(like.device))
+    return ws
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -293,17 +307,15 @@ def _linear_shapes(x, W):
     return x.numel() // K, W.shape[0], K
 
 
-def _linear_workspace(x, W, workspace):
-    """The workspace tensor to pass: given, allocated by torch (None), or none
-    at all (False: the library then takes a path that needs none)."""
-    import torch
-    if workspace is False:
-        return None
+def _linear_workspace(x, M, N, K, dt, workspace, stream=None):
+    """The workspace to pass, with its bytes: given, allocated by torch (None),
+    or none at all (False: the library then takes a path that needs none)."""
     if workspace is None:
-        M, N, K = _linear_shapes(x, W)
-        need = opscale_linear_workspace_size(M, N, K, x.dtype) if M else 0
-        return torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
-    return workspace
+        need = load().opscale_linear_workspace_size(M, N, K, dt) if M else 0
+        return (_scratch(need, x, stream), need) if need else (None, 0)
+    if workspace is False:
+        return None, 0
+    return workspace, workspace.numel() * workspace.element_size()
 
 
 def opscale_linear(x, W, bias=None, y=None, workspace=None, stream=None, timed: bool = False):
@@ -321,14 +333,7 @@ def opscale_linear(x, W, bias=None, y=None, workspace=None, stream=None, timed: 
         y = x.new_empty((*x.shape[:-1], N))
     else:
         _contig("y", y)
-    ws, nbytes = None, 0
-    if workspace is None:
-        nbytes = lib.opscale_linear_workspace_size(M, N, K, dt) if M else 0
-        if nbytes:
-            import torch
-            ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
-    elif workspace is not False:
-        ws, nbytes = workspace, workspace.numel() * workspace.element_size()
+    ws, nbytes = _linear_workspace(x, M, N, K, dt, workspace, stream)
     t = Timing() if timed else None
     _check(lib.opscale_linear(x.data_ptr(), W.data_ptr(), None if bias is None else bias.data_ptr(), y.data_ptr(),
                               M, N, K, dt, None if ws is None else ws.data_ptr(), nbytes, _stream(stream),
@@ -390,7 +395,6 @@ def opscale_attn_decode(q, k_cache, v_cache, block_table, context_lens, max_cont
     q [B, Hq, D] may be strided in its first dimension (a view into the QKV
     output).  block_table int32 [B, max_blocks]; context_lens int32 [B].
     `workspace` (a uint8 GPU tensor) is allocated by torch when not given."""
-    import torch
     lib = load()
     _dev(q, k_cache, v_cache, block_table, context_lens, workspace, out)
     for n, t_ in (("k_cache", k_cache), ("v_cache", v_cache), ("block_table", block_table),
@@ -400,8 +404,7 @@ def opscale_attn_decode(q, k_cache, v_cache, block_table, context_lens, max_cont
     _heads_view("q", q, Hq, D)
     num_blocks, bs, Hkv, _ = k_cache.shape
     if workspace is None:
-        need = lib.opscale_attn_decode_workspace_size(B, Hq, D, max_context_len)
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = _scratch(lib.opscale_attn_decode_workspace_size(B, Hq, D, max_context_len), q, stream)
     if out is None:
         out = q.new_empty((B, Hq, D))
     _contig("out", out)
@@ -543,8 +546,7 @@ def opscale_fused_moe(x, w1, w2, topk_ids, topk_weights, out=None, workspace=Non
     topk = topk_ids.shape[1]
     out = torch.empty_like(x) if out is None else out
     if workspace is None:
-        need = opscale_fused_moe_workspace_size(T, H, F2 // 2, E, topk)
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x.device)
+        workspace = _scratch(max(opscale_fused_moe_workspace_size(T, H, F2 // 2, E, topk), 1), x, stream)
     t = Timing() if timed else None
     _check(load().opscale_fused_moe(_ptr(x), _ptr(w1), _ptr(w2), _ptr(topk_ids), _ptr(topk_weights), _ptr(out), T,
                                     H, F2 // 2, E, topk, _dt(x), _ptr(workspace),
@@ -668,9 +670,8 @@ def desc_linear(x, W, y, bias=None, workspace=None) -> OpDesc:
     opscale_linear for None / False)."""
     d = OpDesc(op=OP_LINEAR, dt=_dt(x))
     M, N, K = _linear_shapes(x, W)
-    ws = _linear_workspace(x, W, workspace)
-    d.u.linear = _LinearArgs(_ptr(x), _ptr(W), _ptr(bias), _ptr(y), M, N, K, _ptr(ws),
-                             0 if ws is None else ws.numel() * ws.element_size())
+    ws, nbytes = _linear_workspace(x, M, N, K, d.dt, workspace)
+    d.u.linear = _LinearArgs(_ptr(x), _ptr(W), _ptr(bias), _ptr(y), M, N, K, _ptr(ws), nbytes)
     d._keep = ws
     return d
 

@@ -676,3 +676,55 @@ def test_attn_decode_context_beyond_launch_bound(ops, bs):
     say(f"attn_decode context beyond max_context_len, bs={bs}")
     got, ref = _decode_case(ops, "bf16", [2000, 700, 3], 8, 2, 128, bs, max_context_len=100)
     assert_close(got, ref, "bf16", "attn_decode long context")
+
+
+# ------------------------------------------------------- temporary workspaces --
+@pytest.mark.parametrize("op", ["linear", "attn_decode", "fused_moe"])
+def test_temporary_workspace_on_another_stream(ops, op):
+    """A workspace that the binding allocates for a call on another stream is
+    not handed on while that stream still has the call before it."""
+    import torch
+    bf = torch.bfloat16
+    if op == "linear":
+        x, W, y = torch.randn(16, 4096, device="cuda").to(bf), torch.randn(6144, 4096, device="cuda").to(bf), None
+        y = torch.empty(16, 6144, device="cuda", dtype=bf)
+        need = ops.opscale_linear_workspace_size(16, 6144, 4096)
+        call = lambda s: ops.opscale_linear(x, W, y=y, stream=s)
+    elif op == "attn_decode":
+        q, out = torch.randn(2, 8, 64, device="cuda").to(bf), torch.empty(2, 8, 64, device="cuda", dtype=bf)
+        kc = torch.randn(64, 16, 2, 64, device="cuda").to(bf)
+        table = torch.arange(64, device="cuda", dtype=torch.int32).view(2, 32)
+        ctx = torch.tensor([512, 500], device="cuda", dtype=torch.int32)
+        need = ops.opscale_attn_decode_workspace_size(2, 8, 64, 512)
+        call = lambda s: ops.opscale_attn_decode(q, kc, kc, table, ctx, 512, 0.125, out=out, stream=s)
+    else:
+        x, out = torch.randn(32, 64, device="cuda").to(bf), torch.empty(32, 64, device="cuda", dtype=bf)
+        w1, w2 = torch.randn(4, 256, 64, device="cuda").to(bf), torch.randn(4, 64, 128, device="cuda").to(bf)
+        ids = torch.zeros(32, 2, device="cuda", dtype=torch.int32)
+        wts = torch.ones(32, 2, device="cuda")
+        need = ops.opscale_fused_moe_workspace_size(32, 64, 128, 4, 2)
+        call = lambda s: ops.opscale_fused_moe(x, w1, w2, ids, wts, out=out, stream=s)
+    assert need > 0
+    say(f"temporary workspace on another stream: {op}, {need} bytes")
+    call(None)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for stream in (side, side.cuda_stream):  # a torch stream, and its handle
+        spot = torch.empty(need, dtype=torch.uint8, device="cuda")
+        p = spot.data_ptr()
+        del spot  # the block that the next allocation of this size gets
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)  # (bounded: about 10 ms)
+        call(stream)
+        again = torch.empty(need, dtype=torch.uint8, device="cuda")
+        assert not side.query(), "the other stream was done too early to tell"
+        assert again.data_ptr() != p, "the workspace was handed on while in use"
+        del again
+        torch.cuda.synchronize()
+    # on the current stream it may be: work there is in order
+    spot = torch.empty(need, dtype=torch.uint8, device="cuda")
+    p = spot.data_ptr()
+    del spot
+    call(torch.cuda.current_stream())
+    assert torch.empty(need, dtype=torch.uint8, device="cuda").data_ptr() == p
+    torch.cuda.synchronize()
