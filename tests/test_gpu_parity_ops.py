@@ -100,7 +100,7 @@ def test_linear_f32_tiles(ops, M, N, K, bias):
 @pytest.mark.parametrize("M,N,K,bias", [(300, 264, 200, True), (513, 1024, 4096, False), (1, 256, 64, False),
                                         (700, 520, 136, False)])
 def test_linear_each_tile(ops, tune, tile, M, N, K, bias):
-    """Every bf16 tile shape the dispatcher can pick, with ragged M, N and K."""
+    """Every bf16 tile that the tile knob names, with ragged M, N and K."""
     import torch
     say(f"linear bf16 tile={tile} M={M} N={N} K={K} bias={bias}")
     tune(gemm_tile=TILES[tile])
@@ -206,13 +206,15 @@ def test_linear_decode_batch(ops, tune, M, N, K, bias):
 @pytest.mark.parametrize("M,N,K,bias", [
     (16, 10232, 1024, True), (17, 24584, 128, False), (32, 24576, 512, True), (33, 4096, 4096, False),
     (64, 6136, 1536, True), (65, 28672, 192, True), (128, 200, 4672, False), (100, 8, 1152, True), (2, 28664, 64, False),
+    (48, 28664, 4096, True), (20, 57336, 1984, False),
 ])
 def test_linear_decode_batch_shapes(ops, tune, M, N, K, bias):
     """The weight-streaming kernel at its edges: the most and fewest rows of
     each row-block count (16, 32, 64, 128), five to eight waves of 16 columns
-    with a ragged last workgroup, one to nine K ranges of one to 64 slices
+    with a ragged last workgroup, one to nine K ranges of one to nine slices
     (each workgroup starting at another one), fewer slices than the ring
-    holds and a partial last round of it."""
+    holds and a partial last round of it; the last two shapes keep K whole: 64
+    and 31 slices, eight and four rounds of the ring, which wraps in the middle."""
     import torch
     tune(gemm_decode=1)
     say(f"linear bf16 decode-batch shapes M={M} N={N} K={K} bias={bias}")
@@ -252,13 +254,19 @@ def test_linear_small_m_workspace_too_small(ops, M):
 @pytest.mark.parametrize("M,N,K,bias", [
     (129, 264, 64, True), (130, 8, 200, False), (256, 520, 128, True), (385, 1032, 192, False), (257, 2056, 1000, True),
     (140, 5000, 1096, False), (256, 4096, 2048, True), (300, 776, 3080, True), (512, 4104, 4096, False),
+    (1224, 1856, 8920, True), (1079, 13256, 584, True),
 ])
 def test_linear_128_row_tiles(ops, tune, M, N, K, bias):
     """Past 128 rows and few 256x256 tiles: the 128x256 tile, whole (each
     column tile starting at another slice of K, one to 16 slices, the last a
     part of one) and split over K (ranges of 8 slices and more, the last one
-    ragged), ragged M and N, through a poisoned workspace and without one."""
+    ragged), ragged M and N, through a poisoned workspace and without one; the
+    last two shapes have nine and ten rows of tiles (a whole group of eight and a
+    part of one), K past 8192, and 468 tiles (more than a round)."""
     import torch
+    TILED, H4 = 2, 6
+    plan = linear_plan(M, N, K)
+    assert (plan.path, plan.cfg) == (TILED, H4), "not the 128x256 tile any more: take other sizes"
     say(f"linear bf16 128-row tiles M={M} N={N} K={K} bias={bias}")
     x = gen(32, "x", (M, K), "bf16")
     W = gen(32, "w_qkv", (N, K), "bf16", std=0.02)
