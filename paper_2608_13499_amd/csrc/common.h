@@ -125,17 +125,18 @@ __device__ __forceinline__ float wave_sum_f(float v) {
 }
 
 // A row's sum over its WPR waves (1, or the 4 of the workgroup), given each
-// lane's part; every lane of the row gets it.  Fixed order.
+// lane's part; every lane of the row gets it.  Fixed order, in pairs: added one
+// after the other, the waves' sums round twice near their full size (fp32 RMS
+// Norm of 3584, error against 64 bits 5.38e-8 where a wave per row has 5.23e-8).
 template <int WPR>
 __device__ __forceinline__ float row_sum(float v) {
+  static_assert(WPR == 1 || WPR == 4, "a wave or a workgroup of four");
   v = wave_sum_f(v);
   if constexpr (WPR > 1) {
     __shared__ float part[WPR];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
-    v = part[0];
-#pragma unroll
-    for (int w = 1; w < WPR; ++w) v += part[w];
+    v = (part[0] + part[1]) + (part[2] + part[3]);
   }
   return v;
 }
