@@ -758,11 +758,12 @@ hipError_t launch_attn_decode(const void* q, int64_t q_stride, const void* kcach
   const dim3 cgrid((unsigned)Hq, (unsigned)B);
   const int max_keys = max_blocks << log2bs;
   __bf16* ob = static_cast<__bf16*>(o);
-  // From 16 workgroups, so about as many segments, a sequence on the four waves
-  // win or draw (us, one wave / four, 64 heads of 128: 1 x 2048 tokens 15.8 / 13.0, 4
-  // x 1024 15.4 / 14.4, 16 x 4096, with 16, 49.8 / 50.0); with fewer they find too
-  // little to share (24 x 700, with 10, 27.9 / 29.0; 32 x 512, with 8, 23.3 / 25.8).
-  const bool many = nwg >= 16 * B;
+  // Past 16 workgroups, so about as many segments, a sequence four waves are
+  // faster (us, one wave / four, 64 heads of 128: 1 x 2048 tokens 15.8 / 13.0, 4 x 1024
+  // 15.4 / 14.4); with 16 or fewer they find too little to share (16 x 4096, with 16,
+  // 49.8 / 50.0 and on half of the CUs 74.9 / 77.4; 24 x 700, with 10, 27.9 / 29.0; 32 x
+  // 512, with 8, 23.3 / 25.8).
+  const bool many = nwg > 16 * B;
 #define OPS_COMB_W(DD, II, WW)                                                                              \
   hipLaunchKernelGGL((attn_decode_combine_kernel<DD, II, WW>), cgrid, dim3(64 * WW), 0, s, ws_o,          \
                      reinterpret_cast<const float2*>(ws_ml), w.tcs, ctx, max_keys, ob, Hq, B, nwg)

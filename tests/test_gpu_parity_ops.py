@@ -636,11 +636,11 @@ def test_attn_decode(ops, dtype, ctx, Hq, Hkv, D, bs):
 @pytest.mark.parametrize("ctx", [[1], [33, 0], [512, 32 * 16 + 1], [32 * 63, 40], [32 * 65 + 5, 31, 1],
                                  [9000, 0, 70, 5, 17, 300, 64, 33]])
 def test_attn_decode_many_segments(ops, ctx, D):
-    """Few sequences over at least 16 workgroups each (launches for contexts of
+    """Few sequences over more than 16 workgroups each (launches for contexts of
     2048 and more): the merge by four waves of 16 segments, at one segment, one
     wave's 16 and one more, 63 to 66 (a second block of 64), and with most of a
     batch's segments in one sequence; and over the workgroups that the contexts
-    themselves give, fewer than 16 a sequence (one wave) for the short ones."""
+    themselves give, at most 16 a sequence (one wave) for the short ones."""
     say(f"attn_decode many segments ctx={ctx} D={D}")
     for maxc in (max(2048, max(ctx)), None):
         got, ref = _decode_case(ops, "bf16", ctx, 8, 2, D, 16, max_context_len=maxc)
