@@ -137,7 +137,8 @@ size_t opscale_linear_workspace_size(int64_t M, int64_t N, int64_t K, opscale_dt
  *   bytes, else OPSCALE_ERR_WORKSPACE with nothing enqueued (up to 32 rows, or
  *   129 to 256 of more than 16384 columns, may take a path that needs none).  Its contents on
  *   entry are ignored; calls sharing a workspace must be stream-ordered.
- *   Split partials are summed in a fixed order, so results are deterministic.
+ *   Split partials are summed in a fixed order, so results are deterministic
+ *   (on streams of different CU masks up to 128 rows may sum K in another order).
  */
 opscale_status opscale_linear(const void* x, const void* W, const void* bias, void* y,
                               int64_t M, int64_t N, int64_t K, opscale_dtype dt,

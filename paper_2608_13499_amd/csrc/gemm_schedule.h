@@ -96,4 +96,26 @@ inline bool grouped_deep_ring(int64_t rows, int64_t N, int64_t E) {
   return last > 0 && last <= kNumCUs;
 }
 
+// The decode-batch linear on a stream of fewer CUs (a CU mask): the waves, of 16
+// columns each, per workgroup that give a CU the fewest columns, K in `splits`
+// ranges.  The shape for the whole chip is often exactly a workgroup per CU, which
+// leaves some CUs two on any smaller share (us, 48 x 28672 x 4096 on 230 CUs, 256
+// workgroups of seven waves 75, 224 of eight 46; on 192 74, 359 of five 59; 48 x
+// 6144 x 4096 on 192, 256 of six 25.7, 192 of eight 19.4).  Workgroups are dealt
+// evenly to the 32 shader engines, so a share counts as 32 times its whole CUs per
+// engine (154 CUs, 299 workgroups: as 128 CUs, three on some).
+constexpr int kMinStreamWaves = 5, kMaxStreamWaves = 8;
+constexpr int kEngines = 32;
+inline int stream_waves(int64_t N, int splits, int cus) {
+  const int even = cus < kEngines ? cus : cus / kEngines * kEngines;
+  int best = 0;
+  int64_t best_cost = 0;
+  for (int nw = kMaxStreamWaves; nw >= kMinStreamWaves; --nw) {
+    const int64_t wgs = (N + 16 * nw - 1) / (16 * nw) * splits;
+    const int64_t cost = (wgs + even - 1) / even * nw;
+    if (best == 0 || cost < best_cost) best = nw, best_cost = cost;
+  }
+  return best;
+}
+
 }  // namespace opscale

@@ -30,18 +30,17 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_schedule.h"
 #include "launch.h"
 
 namespace opscale {
 
 namespace {
 
-constexpr int kNumCUs = 256;
 constexpr int kBK = 64;       // K per slice
 constexpr int kSlots = 8;     // weight ring (registers)
 constexpr int kAhead = 7;     // weight slices in flight beyond the one in use
 constexpr int kStages = 4;    // x ring (LDS)
-constexpr int kMinWaves = 5, kMaxWaves = 8;
 static_assert(kAhead == kSlots - 1 && kSlots % kStages == 0, "ring shapes");
 
 template <int V>
@@ -229,7 +228,7 @@ DecodeShape decode_shape(int64_t N, int64_t K) {
   const int64_t ns = K / kBK;
   DecodeShape best{};
   int64_t best_cost = 0;
-  for (int nw = kMaxWaves; nw >= kMinWaves; --nw) {
+  for (int nw = kMaxStreamWaves; nw >= kMinStreamWaves; --nw) {
     const int64_t tiles = (N + 16 * nw - 1) / (16 * nw);
     const int64_t most = std::max<int64_t>(1, std::min<int64_t>(kNumCUs / tiles, ns / 8));
     const int64_t chunk = (ns + most - 1) / most, splits = (ns + chunk - 1) / chunk;
@@ -277,10 +276,13 @@ hipError_t launch_linear_decode(const void* x, const void* W, const void* bias, 
   const DecodeShape sh = decode_shape(N, K);
   const int nsplit = splits > 1 ? sh.splits : 1;
   const int64_t chunk = splits > 1 ? sh.chunk : K / kBK;
+  // (the K ranges are fixed with the workspace, the columns of a workgroup are not)
+  const int cus = stream_cus(s);
+  const int waves = cus < kNumCUs ? stream_waves(N, nsplit, cus) : sh.waves;
   const auto rows = [&](auto tm_c) {
     constexpr int TM = decltype(tm_c)::value;
     float* part = static_cast<float*>(ws);
-    switch (sh.waves) {
+    switch (waves) {
       case 5: return launch_decode<TM, 5>(x, W, bias, y, M, N, K, nsplit, chunk, part, s);
       case 6: return launch_decode<TM, 6>(x, W, bias, y, M, N, K, nsplit, chunk, part, s);
       case 7: return launch_decode<TM, 7>(x, W, bias, y, M, N, K, nsplit, chunk, part, s);

@@ -14,6 +14,10 @@ namespace opscale {
 // -1 means automatic (the shape decides).
 int32_t tuning(opscale_tune knob);
 
+// The CUs that a stream's kernels may run on: those of its CU mask, all 256 where
+// it has none.
+int stream_cus(hipStream_t s);
+
 // RMS Norm and residual norm: rows of more than this many 16-byte vectors take
 // a workgroup each, shorter ones a wave (a workgroup would have idle lanes; so do
 // large batches of not much longer rows in the RMS Norm, launch_rmsnorm).

@@ -9,6 +9,7 @@
 #include <set>
 #include <vector>
 
+#include "launch.h"
 #include "opscale.h"
 #include "status.h"
 
@@ -67,6 +68,18 @@ opscale_status probe_xcds(const std::vector<uint32_t>& mask, int nwg, std::set<u
 }
 
 }  // namespace
+
+int stream_cus(hipStream_t s) {
+  constexpr int kCus = 256;
+  uint32_t mask[kCus / 32] = {};
+  if (hipExtStreamGetCUMask(s, kCus / 32, mask) != hipSuccess) {
+    (void)hipGetLastError();  // (not this call's error to report)
+    return kCus;
+  }
+  const int n = popcount_words(mask, kCus / 32);
+  return n > 0 ? n : kCus;
+}
+
 }  // namespace opscale
 
 using opscale::fail;

@@ -151,3 +151,31 @@ def test_share_sensitivity_prefill_vs_decode(ops, layout):
             f"(x{res[tokens]:.2f})")
     assert res[2048] > 2.0
     assert res[1] < res[2048]
+
+
+@pytest.mark.parametrize("cus", [13, 100, 192, 230, 255])
+@pytest.mark.parametrize("M,N,K", [(48, 6144, 4096), (20, 28664, 512), (128, 200, 4672)])
+def test_decode_linear_on_a_share(ops, layout, M, N, K, cus):
+    """The decode-batch linear chooses the columns of a workgroup by the
+    stream's CUs (csrc/gemm_schedule.h, stream_waves): five to eight waves, K
+    whole and in the ranges that the workspace was sized for, against the
+    oracle, and again with its poisoned workspace's contents used up."""
+    import torch
+    from oracle import ops as oracle
+    from parity_util import assert_close, cuda, f64, gen
+    say(f"linear {M}x{N}x{K} on {cus} CUs")
+    x, W = gen(31, "x", (M, K), "bf16"), gen(31, "w_qkv", (N, K), "bf16", std=0.02)
+    xd, Wd = cuda(x), cuda(W)
+    need = ops.opscale_linear_workspace_size(M, N, K)
+    ws = torch.full((max(need, 16),), 0x7f, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    n, xcds, il = layout
+    s = ops.opscale_cu_stream_create(ops.opscale_cu_mask_build(n, xcds, il, 0, cus))
+    try:
+        y = ops.opscale_linear(xd, Wd, workspace=ws, stream=s)
+        y2 = ops.opscale_linear(xd, Wd, workspace=ws, stream=s)
+        torch.cuda.synchronize()
+    finally:
+        ops.opscale_cu_stream_destroy(s)
+    assert torch.equal(y, y2)
+    assert_close(f64(y.cpu()), oracle.linear(f64(x), f64(W), None), "bf16", "linear")

@@ -43,6 +43,7 @@ int rows(int64_t M, int per_wg, int64_t* out, int most) {
 }
 double moe_tiles(int64_t rows, int64_t N, int64_t E) { return grouped_tiles(rows, N, E); }
 int moe_deep(int64_t rows, int64_t N, int64_t E) { return grouped_deep_ring(rows, N, E); }
+int waves(int64_t N, int splits, int cus) { return stream_waves(N, splits, cus); }
 void chain(int group, int rounds, int chained, int* out) {
   const Chain c = chain_of(group, rounds, chained != 0);
   out[0] = c.first, out[1] = c.len;
@@ -59,6 +60,7 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
     lib.moe_tiles.argtypes = lib.moe_deep.argtypes = [ctypes.c_int64] * 3
     lib.moe_tiles.restype = ctypes.c_double
+    lib.waves.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     return lib
 
 
@@ -143,6 +145,22 @@ def test_grouped_ring_rule(host):
         assert host.moe_deep(20 * E, 256, E) == deep, E
     # exactly 256 past a whole round (1280 tiles): every one of 64 experts has rows
     assert host.moe_deep(2048, 5120, 64) and not host.moe_deep(2048, 3584, 64)
+
+
+# ------------------------------------------- the decode-batch linear's waves ---
+@pytest.mark.parametrize("cus", [8, 13, 26, 64, 128, 154, 192, 205, 230, 243, 255])
+def test_stream_waves_on_a_share_of_the_cus(host, cus):
+    """On no share does another workgroup shape give a CU fewer columns, the
+    workgroups dealt evenly to the 32 shader engines."""
+    even = cus if cus < 32 else cus // 32 * 32
+    for N in list(range(8, 3000, 56)) + list(range(3000, 60000, 488)) + [4096, 6144, 10240, 28672, 57344]:
+        for splits in (1, 2, 3, 4, 8):
+            wgs = lambda w: -(-N // (16 * w)) * splits
+            cost = lambda w: -(-wgs(w) // even) * w
+            assert cost(host.waves(N, splits, cus)) == min(cost(w) for w in (5, 6, 7, 8)), (N, splits)
+    # gate-up and QKV of the 8B layer: whole passes
+    for share, gate_up, qkv in ((255, 8, 7), (230, 8, 7), (205, 5, 8), (192, 5, 8), (154, 7, 6), (128, 7, 6)):
+        assert (host.waves(28672, 1, share), host.waves(6144, 4, share)) == (gate_up, qkv), share
 
 
 # ------------------------------------------------- fp32 prefill attention ---
