@@ -90,8 +90,11 @@ inline double grouped_tiles(int64_t rows, int64_t N, int64_t E) {
 // 800 473 / 503, 1372 761 / 766), one of up to 256 the reverse (672 563 / 530, 1160
 // 586 / 561, 1280 645 / 629).  The same over 12 expert shapes of 1 to 512 tokens, K of
 // 768 to 14336.  (Weights that fit the last-level cache, e.g. one expert called over and
-// over, go 1-3 us the other way below 130 tiles, 18 at 8 tiles of K = 8192.)
-inline bool grouped_deep_ring(int64_t rows, int64_t N, int64_t E) {
+// over, go 1-3 us the other way below 130 tiles, 18 at 8 tiles of K = 8192.)  On a
+// share of the CUs the estimate is too coarse for the shorter rounds: pairs (64
+// experts of 2560 on 64 CUs, 64 tokens 1337 / 1451, 256 tokens 1440 / 1517).
+inline bool grouped_deep_ring(int64_t rows, int64_t N, int64_t E, int cus) {
+  if (cus < kNumCUs) return false;
   const double last = std::fmod(std::round(grouped_tiles(rows, N, E)), 2.0 * kNumCUs);
   return last > 0 && last <= kNumCUs;
 }

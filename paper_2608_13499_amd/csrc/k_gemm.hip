@@ -1561,7 +1561,7 @@ hipError_t launch_gemm_grouped(const void* x, int64_t x_rows, const void* W, int
                                hipStream_t s) {
   // Decode batches: one workgroup per CU with a deep ring, or two with a shallow one.
   if (tile_rows == CfgRow64::BM) {
-    const bool deep = grouped_deep_ring(max_rows, N, E);
+    const bool deep = grouped_deep_ring(max_rows, N, E, stream_cus(s));
     return deep ? launch_grouped<CfgSk64>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f, s)
                 : launch_grouped<CfgRow64>(x, x_rows, W, w_stride, y, max_rows, N, K, E, gather, rows, tiles, swiglu_f,
                                            s);

@@ -42,7 +42,7 @@ int rows(int64_t M, int per_wg, int64_t* out, int most) {
   return n;
 }
 double moe_tiles(int64_t rows, int64_t N, int64_t E) { return grouped_tiles(rows, N, E); }
-int moe_deep(int64_t rows, int64_t N, int64_t E) { return grouped_deep_ring(rows, N, E); }
+int moe_deep(int64_t rows, int64_t N, int64_t E, int cus) { return grouped_deep_ring(rows, N, E, cus); }
 int waves(int64_t N, int splits, int cus) { return stream_waves(N, splits, cus); }
 void chain(int group, int rounds, int chained, int* out) {
   const Chain c = chain_of(group, rounds, chained != 0);
@@ -58,8 +58,9 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib.attn_f32.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_void_p]
     lib.attn_f32.restype = None
     lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
-    lib.moe_tiles.argtypes = lib.moe_deep.argtypes = [ctypes.c_int64] * 3
+    lib.moe_tiles.argtypes = [ctypes.c_int64] * 3
     lib.moe_tiles.restype = ctypes.c_double
+    lib.moe_deep.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
     lib.waves.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     return lib
 
@@ -142,9 +143,10 @@ def test_grouped_ring_rule(host):
     """The deep ring where the launch's last round of 512 tiles holds at most 256
     (E experts of one column block a tile each; every expert gets a row)."""
     for E, deep in ((1, 1), (84, 1), (250, 1), (262, 0), (336, 0), (500, 0), (520, 1), (760, 1), (780, 0), (1020, 0)):
-        assert host.moe_deep(20 * E, 256, E) == deep, E
+        assert host.moe_deep(20 * E, 256, E, CUS) == deep, E
     # exactly 256 past a whole round (1280 tiles): every one of 64 experts has rows
-    assert host.moe_deep(2048, 5120, 64) and not host.moe_deep(2048, 3584, 64)
+    assert host.moe_deep(2048, 5120, 64, CUS) and not host.moe_deep(2048, 3584, 64, CUS)
+    assert not any(host.moe_deep(20 * E, 256, E, CUS - 1) for E in range(1, 600, 7)), "a share of the CUs: never"
 
 
 # ------------------------------------------- the decode-batch linear's waves ---
