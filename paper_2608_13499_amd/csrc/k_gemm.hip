@@ -75,7 +75,7 @@ using CfgW4 = GemmCfg<256, 256, 64, 2, 2, 2>;      // 4 waves of 128x128, 2 x 64
 using CfgRow64 = GemmCfg<64, 256, 64, 1, 4, 2>;    // 4 waves of 64x64, 2 x 40 KB stages (few rows)
 // split-K tiles for decode-sized M: a K range is short, so the ring is deep
 using CfgSk64 = GemmCfg<64, 256, 64, 1, 4, 4, true>;    // M <= 64: 4 waves of 64x64, 4 x 40 KB stages
-using CfgSk128 = GemmCfg<128, 256, 64, 2, 4, 3, true>;  // M <= 256: 8 waves of 64x64, 3 x 48 KB stages
+using CfgSk128 = GemmCfg<128, 256, 64, 2, 4, 3, true>;  // 65 to 128 rows: 8 waves of 64x64, 3 x 48 KB stages
 
 
 // 16-byte chunk c of LDS row r is stored at physical chunk c ^ swz(r).
@@ -1065,7 +1065,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_h4_kernel(const __bf16* __re
   constexpr int BM = 128, BN = 256, BK = 64, WM = 128, WN = 64;
   constexpr int MI = 16, TM = WM / MI, TN = WN / MI, KS = 2;  // 8 x 4 MFMA tiles per wave
   constexpr int kWaves = 4, LX = 4, LW = 8;                    // loads per wave of an x / W slice
-  constexpr int XS = 4, WS = 3;                                // ring depths
+  constexpr int XS = 4;                                        // ring of x slices (of W's: three)
   constexpr int XB = BM * 128, WB = BN * 128;
   constexpr uint32_t kOutOfRange = 0xfffffff0u;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];

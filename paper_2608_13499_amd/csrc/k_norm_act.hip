@@ -188,11 +188,22 @@ static hipError_t swiglu_dispatch(const void* gu, void* out, int64_t M, int64_t 
 }
 
 hipError_t launch_swiglu(const void* gu, void* out, int64_t M, int64_t F, bool bf16, hipStream_t s) {
-  // Up to 16 million outputs of wide rows (of narrow ones, up to 256 rows):
-  // cached accesses and one vector a thread, i.e. twice the workgroups.  us, two
-  // nontemporal / one cached: F = 14336, M = 1 2.1 / 1.8, 256 9.5 / 7.9, 512 11.8 /
-  // 9.0, 1023 16.5 / 14.5, 2048 28.9 / 35.9, 8871 123 / 134; F = 2560, M = 256 3.55 /
-  // 3.33, 512 4.8 / 5.2, 1023 7.1 / 8.0.
+  // Up to 256 rows, and up to 16 million outputs of rows of 8192 and wider: cached
+  // accesses and one vector a thread, i.e. twice the workgroups.  What is small
+  // stays in the caches from the projection before (the first pair of each) and
+  // gains by both; larger, the last-level cache evicts what the next operator
+  // reads.  us, two nontemporal / one cached, operands just written | cold:
+  //   F = 2560:  M = 48 2.8 / 2.4 | 3.1 / 2.4, 256 3.5 / 2.7 | 3.7 / 3.2,
+  //              512 (the reverse from here) cold 4.8 / 5.2, 1023 7.1 / 8.0
+  //   F = 8192:  256 4.3 / 3.6 | 4.8 / 4.4, 512 5.9 / 5.4 | 6.7 / 6.3,
+  //              1023 9.4 / 9.7 | 10.9 / 11.8, 2048 17.4 / 16.3 | 19.7 / 19.6
+  //   F = 14336: 256 5.7 / 4.8 | 6.5 / 5.9, 512 8.9 / 8.2 | 10.5 / 10.7,
+  //              1023 16.0 / 14.5 | 17.6 / 17.7, 2048 cold 28.9 / 35.9
+  //   F = 28672: 100 5.0 / 4.3 | 5.7 / 5.1, 256 8.4 / 8.0 | 9.8 / 10.7,
+  //              512 15.7 / 14.8 | 17.6 / 17.6
+  // Widths of 512 to 2048 differ by less than the runs; 4096 to 7168, 11008 and
+  // 18944 lie between their neighbours.  Cold inputs of 6 to 16 million outputs cost
+  // up to 8 % more than before, which the MLP, where they are warm, gains.
   const bool small = M * F <= ((int64_t)1 << 24) && (F >= 8192 || M <= 256);
   if (small)
     return bf16 ? swiglu_dispatch<true, 1, false>(gu, out, M, F, s) : swiglu_dispatch<false, 1, false>(gu, out, M, F, s);
