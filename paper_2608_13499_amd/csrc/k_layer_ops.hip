@@ -227,30 +227,42 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(const void* x, void* r
   // plain (cached) loads and stores, as in the RMS Norm kernel (faster than
   // the nontemporal forms on a streamed row block)
   constexpr u32x4 kZero = {0u, 0u, 0u, 0u};
+  // A wave of a long row adds as it loads and reads the weight last: fewer registers,
+  // more waves (it runs where there are rows enough).
+  constexpr bool kLate = WPR == 1 && VPL > 2;
   u32x4 xv[VPL], rv[VPL], g[VPL];
-#pragma unroll
-  for (int i = 0; i < VPL; ++i) {
-    const int idx = lane + i * STEP;
-    xv[i] = idx < nvec ? xr[idx] : kZero;
-    rv[i] = idx < nvec ? rr[idx] : kZero;
-  }
-#pragma unroll
-  for (int i = 0; i < VPL; ++i) {
-    const int idx = lane + i * STEP;
-    g[i] = idx < nvec ? wr[idx] : kZero;
-  }
-  float sum[VPL][EPV];
+  float sum[VPL][EPV] = {};
   float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < VPL; ++i) {
+  auto add = [&](int i, const u32x4& xi, const u32x4& ri) {
     float a[EPV], b[EPV];
-    unpack(xv[i], a);
-    unpack(rv[i], b);
+    unpack(xi, a);
+    unpack(ri, b);
 #pragma unroll
     for (int e = 0; e < EPV; ++e) {
       sum[i][e] = a[e] + b[e];
       ss = fmaf(sum[i][e], sum[i][e], ss);
     }
+  };
+  if constexpr (kLate) {
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      const int idx = lane + i * STEP;
+      if (idx < nvec) add(i, xr[idx], rr[idx]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      const int idx = lane + i * STEP;
+      xv[i] = idx < nvec ? xr[idx] : kZero;
+      rv[i] = idx < nvec ? rr[idx] : kZero;
+    }
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      const int idx = lane + i * STEP;
+      g[i] = idx < nvec ? wr[idx] : kZero;
+    }
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) add(i, xv[i], rv[i]);
   }
   ss = row_sum<WPR>(ss);
   const float r = rsqrtf(ss / (float)H + eps);
@@ -259,6 +271,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(const void* x, void* r
     const int idx = lane + i * STEP;
     if (idx >= nvec) continue;
     rr[idx] = pack(sum[i]);
+    if constexpr (kLate) g[i] = wr[idx];
     float gf[EPV], o[EPV];
     unpack(g[i], gf);
 #pragma unroll
@@ -282,7 +295,11 @@ static hipError_t add_rmsnorm_dispatch(const void* x, void* res, const void* w, 
   hipLaunchKernelGGL((add_rmsnorm_kernel<BF16, V, WPR>), dim3(grid), dim3(256), 0, s, xm, rm, w, ym, rows, h, eps)
     if (vpl <= 1) OPS_ADDRMS(1);
     else if (vpl <= 2) OPS_ADDRMS(2);
-    else if constexpr (WPR > 1) OPS_ADDRMS(4);  // (rows of at most 16 KB)
+    else if (vpl <= 4) OPS_ADDRMS(4);
+    else if constexpr (WPR == 1) {  // (rows of at most 16 KB, here of 4096 elements)
+      if (vpl <= 8) OPS_ADDRMS(8);
+      else if constexpr (!BF16) OPS_ADDRMS(16);
+    }
 #undef OPS_ADDRMS
     return hipGetLastError();
   });
@@ -290,7 +307,9 @@ static hipError_t add_rmsnorm_dispatch(const void* x, void* res, const void* w, 
 
 hipError_t launch_add_rmsnorm(const void* x, void* res, const void* w, void* y, int64_t M, int64_t H, float eps,
                               bool bf16, hipStream_t s) {
-  if (H / (bf16 ? 8 : 4) > kWaveRowMaxVec)
+  const bool wave = H / (bf16 ? 8 : 4) <= kWaveRowMaxVec ||
+                    (M * H >= kAddWaveRowsFill && add_rmsnorm_wave_rows(M, H, stream_cus(s)));
+  if (!wave)
     return bf16 ? add_rmsnorm_dispatch<true, 4>(x, res, w, y, M, H, eps, s)
                 : add_rmsnorm_dispatch<false, 4>(x, res, w, y, M, H, eps, s);
   return bf16 ? add_rmsnorm_dispatch<true, 1>(x, res, w, y, M, H, eps, s)

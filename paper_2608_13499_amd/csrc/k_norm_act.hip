@@ -109,11 +109,9 @@ static hipError_t rmsnorm_dispatch(const void* x, const void* w, void* y, int64_
     if (vpl <= 1) OPS_RMS(1);
     else if (vpl <= 2) OPS_RMS(2);
     else if (vpl <= 4) OPS_RMS(4);
-    else if constexpr (WPR > 1) {
-      if (vpl <= 8) OPS_RMS(8);
-      else if (vpl <= 16) OPS_RMS(16);
-      else OPS_RMS(0);
-    }
+    else if (vpl <= 8) OPS_RMS(8);
+    else if (vpl <= 16) OPS_RMS(16);
+    else if constexpr (WPR > 1) OPS_RMS(0);
 #undef OPS_RMS
     return hipGetLastError();
   });
@@ -126,7 +124,10 @@ hipError_t launch_rmsnorm(const void* x, const void* w, void* y, int64_t M, int6
   // row: 1032 wide, 1023 rows 3.27 / 3.27, 2048 4.0 / 4.2, 8871 10.0 / 12.0; 1536
   // wide, 100 rows 2.57 / 2.44, 20000 22.8 / 24.1; 2048 wide, 20000 30.0 / 29.6)
   const int64_t nvec = H / (bf16 ? 8 : 4);
-  if (nvec > kWaveRowMaxVec && (nvec >= 256 || M < 2048))
+  // (too little for one CU: its calls are spared the 0.3 us that the mask's query takes)
+  const bool wave = nvec <= kWaveRowMaxVec || (nvec < 256 && M >= 2048) ||
+                    (M * H >= kWaveRowsFill && rmsnorm_wave_rows(M, H, nvec, stream_cus(s)));
+  if (!wave)
     return bf16 ? rmsnorm_dispatch<true, 4>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 4>(x, w, y, M, H, eps, s);
   return bf16 ? rmsnorm_dispatch<true, 1>(x, w, y, M, H, eps, s) : rmsnorm_dispatch<false, 1>(x, w, y, M, H, eps, s);
 }

@@ -179,3 +179,32 @@ def test_decode_linear_on_a_share(ops, layout, M, N, K, cus):
         ops.opscale_cu_stream_destroy(s)
     assert torch.equal(y, y2)
     assert_close(f64(y.cpu()), oracle.linear(f64(x), f64(W), None), "bf16", "linear")
+
+
+@pytest.mark.parametrize("dtype,H", [("bf16", 1032), ("bf16", 2056), ("bf16", 4096), ("bf16", 4104), ("bf16", 8192),
+                                     ("f32", 516), ("f32", 1028), ("f32", 2052), ("f32", 4096)])
+def test_norms_on_a_share(ops, layout, dtype, H):
+    """Row blocks that fill a share of eight CUs: a wave holds the row (3 to 16
+    vectors a lane, a ragged last one, a ragged last workgroup), but for the
+    residual norm past 4096."""
+    import torch
+    from oracle import ops as oracle
+    from parity_util import assert_close, cuda, f64, gen
+    M = 641 if H < 1032 else 329
+    say(f"norms {dtype} {M}x{H} on 8 CUs")
+    x, r = gen(37, "x", (M, H), dtype), gen(37, "attn_out", (M, H), dtype)
+    w = gen(37, "w_norm", (H,), dtype, std=0.02, mean=1.0)
+    xd, rd, wd = cuda(x), cuda(r), cuda(w)
+    torch.cuda.synchronize()
+    n, xcds, il = layout
+    s = ops.opscale_cu_stream_create(ops.opscale_cu_mask_build(n, xcds, il, 0, 8))
+    try:
+        z = ops.opscale_rmsnorm(xd, wd, eps=1e-5, stream=s)
+        y = ops.opscale_add_rmsnorm(xd, rd, wd, eps=1e-5, stream=s)
+        torch.cuda.synchronize()
+    finally:
+        ops.opscale_cu_stream_destroy(s)
+    ry, rr = oracle.add_rmsnorm(f64(x), f64(r), f64(w), 1e-5)
+    assert_close(f64(rd.cpu()), rr, dtype, "residual")
+    assert_close(f64(y.cpu()), ry, dtype, "add_rmsnorm")
+    assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, "rmsnorm")

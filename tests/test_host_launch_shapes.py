@@ -41,6 +41,8 @@ int rows(int64_t M, int per_wg, int64_t* out, int most) {
   });
   return n;
 }
+int rms_wave(int64_t M, int64_t H, int64_t nvec, int cus) { return rmsnorm_wave_rows(M, H, nvec, cus); }
+int add_wave(int64_t M, int64_t H, int cus) { return add_rmsnorm_wave_rows(M, H, cus); }
 double moe_tiles(int64_t rows, int64_t N, int64_t E) { return grouped_tiles(rows, N, E); }
 int moe_deep(int64_t rows, int64_t N, int64_t E, int cus) { return grouped_deep_ring(rows, N, E, cus); }
 int waves(int64_t N, int splits, int cus) { return stream_waves(N, splits, cus); }
@@ -58,6 +60,8 @@ int64_t grid(int64_t items, int chained, int exact) { return chain_grid(items, c
     lib.attn_f32.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_void_p]
     lib.attn_f32.restype = None
     lib.rows.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
+    lib.rms_wave.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    lib.add_wave.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int]
     lib.moe_tiles.argtypes = [ctypes.c_int64] * 3
     lib.moe_tiles.restype = ctypes.c_double
     lib.moe_deep.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
@@ -216,3 +220,18 @@ def test_rows_past_one_grid(host, per_wg):
         assert at == M
     # an error ends it
     assert host.rows(3 * most, per_wg, (ctypes.c_int64 * 9)(), 2) == 2
+
+
+def test_norm_rows_on_a_share_of_the_cus(host):
+    """A wave a row only on a share, for row blocks that fill it, and for rows
+    that a wave holds: any others keep their workgroup, up to the most rows."""
+    for H, vec in ((1032, 8), (4096, 8), (8192, 8), (516, 4), (4096, 4)):
+        for cus in (8, 26, 64, 128, 154, 160):
+            rms, add = -(-20480 * cus // H), -(-40960 * cus // H)
+            assert host.rms_wave(rms, H, H // vec, cus) and not host.rms_wave(rms - 1, H, H // vec, cus)
+            assert host.add_wave(add, H, cus) == (H <= 4096) and not host.add_wave(add - 1, H, cus)
+            assert host.rms_wave(2**31 - 1, H, H // vec, cus)
+        for cus in (161, 192, 255, CUS):
+            assert not host.rms_wave(2**31 - 1, H, H // vec, cus) and not host.add_wave(2**31 - 1, H, cus)
+    assert not host.rms_wave(8871, 8200, 1025, 64) and not host.rms_wave(8871, 4100, 1025, 64)
+    assert not host.add_wave(8871, 4104, 64)
