@@ -71,6 +71,8 @@ opscale_status probe_xcds(const std::vector<uint32_t>& mask, int nwg, std::set<u
 
 int stream_cus(hipStream_t s) {
   constexpr int kCus = 256;
+  // (these two are names for streams without a mask, no objects to ask)
+  if (s == hipStreamLegacy || s == hipStreamPerThread) return kCus;
   uint32_t mask[kCus / 32] = {};
   if (hipExtStreamGetCUMask(s, kCus / 32, mask) != hipSuccess) {
     (void)hipGetLastError();  // (not this call's error to report)

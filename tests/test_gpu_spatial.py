@@ -208,3 +208,23 @@ def test_norms_on_a_share(ops, layout, dtype, H):
     assert_close(f64(rd.cpu()), rr, dtype, "residual")
     assert_close(f64(y.cpu()), ry, dtype, "add_rmsnorm")
     assert_close(f64(z.cpu()), oracle.rmsnorm(f64(x), f64(w), 1e-5), dtype, "rmsnorm")
+
+
+@pytest.mark.parametrize("handle", [0, 2, 1], ids=["null", "per-thread", "legacy"])
+def test_handles_that_name_a_stream(ops, handle):
+    """The handles that stand for a stream (hipStreamPerThread, hipStreamLegacy)
+    are taken like any other where the CUs of a stream are asked for."""
+    import torch
+    from parity_util import cuda, gen
+    say(f"stream handle {handle}")
+    x, W = cuda(gen(38, "x", (48, 1024), "bf16")), cuda(gen(38, "w_qkv", (1536, 1024), "bf16", std=0.02))
+    w = cuda(gen(38, "w_norm", (1536,), "bf16", std=0.02, mean=1.0))
+    ws = torch.empty(ops.opscale_linear_workspace_size(48, 1536, 1024), dtype=torch.uint8, device="cuda")
+    a = ops.opscale_linear(x, W, workspace=ws)
+    z = ops.opscale_rmsnorm(a, w)
+    torch.cuda.synchronize()
+    b = ops.opscale_linear(x, W, workspace=ws, stream=handle)
+    torch.cuda.synchronize()
+    y = ops.opscale_rmsnorm(b, w, stream=handle)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and torch.equal(z, y)
